@@ -7,6 +7,7 @@
 // and one round-to-nearest-even to fp16 (gkv::f64_to_f16).
 #include <hip/hip_runtime.h>
 
+#include "encode_block.h"
 #include "gkv_internal.h"
 
 #pragma clang fp contract(off)
@@ -15,360 +16,42 @@ using namespace gkv;
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int XS = D + 1;  // padded LDS row stride (doubles) against bank conflicts
+constexpr int kThreads = enc::kThreads;
+using enc::round_up_f32;
 
-struct EncodeShared {
-  uint16_t xh[P * D];      // source as fp16 bits [token][channel] (rows or exact record)
-  uint8_t xc[P * D];       // source as codes (int-level record being demoted)
-  double xs[D], xz[D];     // source scale / zero for xc
-  int32_t src_int;         // 1: x = xc * xs + xz, 0: x = xh, 2: x = centroid[xc]
-  int32_t src_tok;         // with src_int == 1: xs, xz are per token (index t), else per channel
-  double sc[KC * D];       // source centroids (fp64) when src_int == 2
-  double c[KC * XS];       // centroids (fp64)
-  double dist[P * KC];     // token x centroid distances
-  double s64[D], z64[D];   // new scale / zero
-  uint16_t s16[D], z16[D];
-  uint8_t codes[P * D];    // new codes (int levels)
-  int32_t assign[P], prev[P];
-  int32_t flag;
-  double cert[2];  // block_cert results
-};
-
-// Exact fp64 value of source element (t, d): an fp16 value, or code * scale + zero
-// (both products and the sum are exact in fp64).
-__device__ __forceinline__ double getx(const EncodeShared &S, int t, int d) {
-  if (S.src_int == 2) return S.sc[S.xc[t * D] * D + d];
-  if (S.src_int) {
-    const int g = S.src_tok ? t : d;
-    const double prod = (double)S.xc[t * D + d] * S.xs[g];
-    return prod + S.xz[g];
-  }
-  return (double)__builtin_bit_cast(_Float16, S.xh[t * D + d]);
-}
-
-// Load the 64 x 128 block starting at row0 of one (b,h) from token-major fp16 rows;
-// rows at or beyond T_src read as zero.
-__device__ void load_rows(EncodeShared &S, const uint16_t *src, int64_t T_src, int64_t row0) {
-  if (threadIdx.x == 0) {
-    S.src_int = 0;
-    S.src_tok = 0;
-  }
-  for (int i = threadIdx.x; i < P * (D / 8); i += kThreads) {
-    const int t = i / (D / 8), c8 = (i % (D / 8)) * 8;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (row0 + t < T_src) v = *(const uint4 *)(src + (row0 + t) * D + c8);
-    *(uint4 *)(S.xh + t * D + c8) = v;
-  }
-}
-
-// Load a record as the source (per_token: an int-level value record grouped per token).
-__device__ void load_record(EncodeShared &S, const uint8_t *rec, int level, int tensor, bool per_token) {
-  if (threadIdx.x == 0) S.src_tok = per_token && is_int_level(level);
-  if (level == GKV_EXACT) {
-    if (threadIdx.x == 0) S.src_int = 0;
-    const uint16_t *hh = (const uint16_t *)rec;
-    for (int ck = threadIdx.x; ck < 4 * 64; ck += kThreads) {
-      const int pg = ck >> 6, l = ck & 63;
-      for (int n = 0; n < 32; ++n) {
-        int t, ch;
-        chunk_coord(tensor, pg, l, n, t, ch);
-        S.xh[t * D + ch] = hh[ck * 32 + n];
-      }
-    }
-    return;
-  }
-  if (level == GKV_MEAN) {  // one centroid: every token reads it
-    if (threadIdx.x == 0) S.src_int = 2;
-    const uint16_t *cc = (const uint16_t *)rec;
-    for (int d = threadIdx.x; d < D; d += kThreads) S.sc[d] = (double)__builtin_bit_cast(_Float16, cc[d]);
-    for (int t = threadIdx.x; t < P; t += kThreads) S.xc[t * D] = 0;
-    return;
-  }
-  if (level == GKV_CENTROID) {
-    if (threadIdx.x == 0) S.src_int = 2;
-    const uint16_t *cc = (const uint16_t *)rec;
-    for (int i = threadIdx.x; i < KC * D; i += kThreads) {
-      const int k = i >> 7, d = i & 127;
-      S.sc[i] = (double)__builtin_bit_cast(_Float16, cc[tensor == GKV_KEYS ? k * D + d : vcent_index(k, d)]);
-    }
-    const uint8_t *idb = rec + KC * D * 2;
-    for (int t = threadIdx.x; t < P; t += kThreads) S.xc[t * D] = (idb[t >> 2] >> (2 * (t & 3))) & 3;
-    return;
-  }
-  if (threadIdx.x == 0) S.src_int = 1;
-  const uint16_t *sz = (const uint16_t *)rec;
-  if (per_token) {
-    for (int t = threadIdx.x; t < P; t += kThreads) {
-      S.xs[t] = (double)__builtin_bit_cast(_Float16, sz[t]);
-      S.xz[t] = (double)__builtin_bit_cast(_Float16, sz[P + t]);
-    }
-  } else {
-    for (int e = threadIdx.x; e < D; e += kThreads) {
-      const int ch = sz_channel(tensor, e);
-      S.xs[ch] = (double)__builtin_bit_cast(_Float16, sz[e]);
-      S.xz[ch] = (double)__builtin_bit_cast(_Float16, sz[D + e]);
-    }
-  }
-  const int bits = level;
-  const uint32_t *w = (const uint32_t *)(rec + kSZBytes);
-  for (int ck = threadIdx.x; ck < 4 * 64; ck += kThreads) {
-    const int pg = ck >> 6, l = ck & 63;
-    for (int n = 0; n < 32; ++n) {
-      int t, ch;
-      chunk_coord(tensor, pg, l, n, t, ch);
-      const uint32_t word = w[ck * bits + code_word(bits, n)];
-      S.xc[t * D + ch] = (uint8_t)((word >> code_pos(bits, n)) & ((1u << bits) - 1u));
-    }
-  }
-}
-
-// Exact level: store the fp16 source in chunk order (source must be fp16).
-__device__ void write_exact(EncodeShared &S, uint8_t *dst, int tensor) {
-  uint16_t *hh = (uint16_t *)dst;
-  for (int ck = threadIdx.x; ck < 4 * 64; ck += kThreads) {
-    const int pg = ck >> 6, l = ck & 63;
-    uint32_t w[16];
-    for (int n = 0; n < 32; n += 2) {
-      int t0, c0, t1, c1;
-      chunk_coord(tensor, pg, l, n, t0, c0);
-      chunk_coord(tensor, pg, l, n + 1, t1, c1);
-      w[n >> 1] = (uint32_t)S.xh[t0 * D + c0] | ((uint32_t)S.xh[t1 * D + c1] << 16);
-    }
-    uint4 *o = (uint4 *)(hh + ck * 32);
-    for (int q = 0; q < 4; ++q) o[q] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
-  }
-}
-
-// Scalar quantizer, one group per channel, or per token for a value block of a
-// cache that groups values per token (section 3.2).
-__device__ void encode_int(EncodeShared &S, uint8_t *dst, int bits, int tensor, bool per_token) {
-  const double qmax = (double)((1 << bits) - 1);
-  const int tid = threadIdx.x;
-  if (tid < (per_token ? P : D)) {
-    double mn = per_token ? getx(S, tid, 0) : getx(S, 0, tid), mx = mn;
-    for (int i = 1; i < (per_token ? D : P); ++i) {
-      const double v = per_token ? getx(S, tid, i) : getx(S, i, tid);
-      mn = v < mn ? v : mn;
-      mx = v > mx ? v : mx;
-    }
-    const double range = mx - mn;
-    const uint16_t z = canon_zero(f64_to_f16(mn));
-    const uint16_t s = canon_zero(f64_to_f16(range / qmax));
-    S.z16[tid] = z;
-    S.s16[tid] = s;
-    S.z64[tid] = f16_to_f64(z);
-    S.s64[tid] = f16_to_f64(s);
-  }
-  __syncthreads();
-  for (int i = tid; i < P * D; i += kThreads) {
-    const int t = i >> 7, d = i & 127, g = per_token ? t : d;
-    const double s = S.s64[g];
-    uint8_t code = 0;
-    if (s != 0.0) {
-      const double diff = getx(S, t, d) - S.z64[g];
-      double r = __builtin_rint(diff / s);
-      r = r < 0.0 ? 0.0 : r;
-      r = r > qmax ? qmax : r;
-      code = (uint8_t)r;
-    }
-    S.codes[t * D + d] = code;
-  }
-  __syncthreads();
-  uint16_t *sz = (uint16_t *)dst;
-  if (per_token) {  // scale[64], zero[64] in token order, then zeros
-    for (int e = tid; e < 2 * D; e += kThreads) sz[e] = e < P ? S.s16[e] : (e < 2 * P ? S.z16[e - P] : 0);
-  } else {
-    for (int e = tid; e < D; e += kThreads) {
-      const int ch = sz_channel(tensor, e);
-      sz[e] = S.s16[ch];
-      sz[D + e] = S.z16[ch];
-    }
-  }
-  uint32_t *w = (uint32_t *)(dst + kSZBytes);
-  for (int ck = tid; ck < 4 * 64; ck += kThreads) {
-    const int pg = ck >> 6, l = ck & 63;
-    uint32_t words[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int n = 0; n < 32; ++n) {
-      int t, ch;
-      chunk_coord(tensor, pg, l, n, t, ch);
-      words[code_word(bits, n)] |= (uint32_t)S.codes[t * D + ch] << code_pos(bits, n);
-    }
-    for (int q = 0; q < bits; ++q) w[ck * bits + q] = words[q];
-  }
-}
-
-// Squared distances of every token to every centroid, channel-ascending, no FMA.
-__device__ void kmeans_dist(EncodeShared &S) {
-  const int t = threadIdx.x >> 2, k = threadIdx.x & 3;  // 256 threads = 64 tokens x 4
-  double acc = 0.0;
-  for (int d = 0; d < D; ++d) {
-    const double diff = getx(S, t, d) - S.c[k * XS + d];
-    const double sq = diff * diff;
-    acc = acc + sq;
-  }
-  S.dist[t * KC + k] = acc;
-  __syncthreads();
-  if (threadIdx.x < P) {
-    const int tt = threadIdx.x;
-    int best = 0;
-    double bd = S.dist[tt * KC];
-    for (int kk = 1; kk < KC; ++kk)
-      if (S.dist[tt * KC + kk] < bd) {
-        bd = S.dist[tt * KC + kk];
-        best = kk;
-      }
-    S.assign[tt] = best;
-  }
-  __syncthreads();
-}
-
-// Deterministic 4-means Lloyd iteration, then fp16 centroids and re-assigned ids.
-__device__ void encode_centroid(EncodeShared &S, uint8_t *dst, int tensor) {
-  const int tid = threadIdx.x;
-  for (int i = tid; i < KC * D; i += kThreads) {
-    const int k = i >> 7, d = i & 127;
-    S.c[k * XS + d] = getx(S, k * (P / KC), d);
-  }
-  __syncthreads();
-  for (int it = 0; it < 10; ++it) {
-    kmeans_dist(S);
-    if (tid == 0) S.flag = 0;
-    __syncthreads();
-    if (it > 0 && tid < P && S.assign[tid] != S.prev[tid]) atomicOr(&S.flag, 1);
-    __syncthreads();
-    if (it > 0 && S.flag == 0) break;  // assignment repeated: converged
-    if (tid < P) S.prev[tid] = S.assign[tid];
-    __syncthreads();
-    for (int i = tid; i < KC * D; i += kThreads) {
-      const int k = i >> 7, d = i & 127;
-      double acc = 0.0;
-      int n = 0;
-      for (int t = 0; t < P; ++t)
-        if (S.assign[t] == k) {
-          acc = acc + getx(S, t, d);
-          ++n;
-        }
-      if (n > 0) S.c[k * XS + d] = acc / (double)n;
-    }
-    __syncthreads();
-  }
-  // round the centroids to fp16 and assign against what is stored
-  uint16_t *cc = (uint16_t *)dst;
-  for (int i = tid; i < KC * D; i += kThreads) {
-    const int k = i >> 7, d = i & 127;
-    const uint16_t h = canon_zero(f64_to_f16(S.c[k * XS + d]));
-    S.c[k * XS + d] = f16_to_f64(h);
-    cc[tensor == GKV_KEYS ? k * D + d : vcent_index(k, d)] = h;
-  }
-  __syncthreads();
-  kmeans_dist(S);
-  if (tid < P / 16) {
-    uint32_t w = 0;
-    for (int j = 0; j < 16; ++j) w |= (uint32_t)S.assign[tid * 16 + j] << (2 * j);
-    ((uint32_t *)(dst + KC * D * 2))[tid] = w;
-  }
-}
-
-// One-centroid state: the Lloyd iteration with one centroid converges in one
-// update to the block mean; the fp64 token-ascending sum of 64 fp16 values (or of
-// decoded values) is the same sum the iteration takes, then one fp16 rounding.
-__device__ void encode_mean(EncodeShared &S, uint8_t *dst) {
-  const int tid = threadIdx.x;
-  if (tid < D) {
-    double acc = 0.0;
-    for (int t = 0; t < P; ++t) acc = acc + getx(S, t, tid);
-    const uint16_t h = canon_zero(f64_to_f16(acc / (double)P));
-    S.c[tid] = f16_to_f64(h);  // centroid 0, for the certificate
-    ((uint16_t *)dst)[tid] = h;
-  }
-  if (tid < P) S.assign[tid] = 0;
-}
-
-__device__ void encode_to(EncodeShared &S, uint8_t *dst, int level, int tensor, bool per_token) {
-  if (level == GKV_EXACT) write_exact(S, dst, tensor);
-  else if (is_int_level(level)) encode_int(S, dst, level, tensor, per_token);
-  else if (level == GKV_MEAN) encode_mean(S, dst);
-  else encode_centroid(S, dst, tensor);
-}
-
-// Non-negative fp64 -> fp32 rounded towards +inf (the certificate keeps upper
-// bounds): one ulp up when the nearest float lies below.
-__device__ __forceinline__ float round_up_f32(double x) {
-  float f = (float)x;
-  if ((double)f < x) f = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, f) + 1u);
-  return f;
-}
-
-// Certificate numbers of the block just encoded at `level` from the source in S:
-// err = max_t ||x_t - x_hat_t|| and nrm = max_t ||x_t|| over the 64 rows (fp64; x is
-// the source, x_hat the new record's reconstruction).  256 threads: 4 per row, 32
-// channels each.  Result in S.cert[0..1].
-__device__ void block_cert(EncodeShared &S, int level, bool per_token) {
-  const int t = threadIdx.x >> 2, j = threadIdx.x & 3;
-  double e = 0.0, n = 0.0;
-  for (int d = 32 * j; d < 32 * j + 32; ++d) {
-    const double x = getx(S, t, d);
-    double xh = x;
-    if (is_int_level(level)) {
-      const int g = per_token ? t : d;
-      xh = (double)S.codes[t * D + d] * S.s64[g] + S.z64[g];
-    }
-    else if (level == GKV_CENTROID || level == GKV_MEAN) xh = S.c[S.assign[t] * XS + d];
-    e += (x - xh) * (x - xh);
-    n += x * x;
-  }
-  e += __shfl_xor(e, 1);
-  e += __shfl_xor(e, 2);
-  n += __shfl_xor(n, 1);
-  n += __shfl_xor(n, 2);
-  if (j == 0) {
-    S.dist[t * KC] = e;  // scratch: the k-means distances are no longer needed
-    S.dist[t * KC + 1] = n;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double me = 0.0, mn = 0.0;
-    for (int r = 0; r < P; ++r) {
-      me = S.dist[r * KC] > me ? S.dist[r * KC] : me;
-      mn = S.dist[r * KC + 1] > mn ? S.dist[r * KC + 1] : mn;
-    }
-    S.cert[0] = __builtin_sqrt(me);
-    S.cert[1] = __builtin_sqrt(mn);
-  }
-  __syncthreads();
-}
-
-// Prefill encode: one workgroup per (block, h, b) of one tensor.
-__global__ void __launch_bounds__(kThreads) quantize_kernel(const uint16_t *__restrict__ src, int64_t T_src,
+// Prefill encode: one workgroup per (block, h, b) of one tensor.  128k tokens x 8 heads of
+// the graded ladder: 140 us for the keys, 142 us for the values (352 MB each, 2.5 TB/s;
+// 1357 us each with the block staged in LDS and every element's quotient and error in
+// fp64).  Vector instructions bound it: 670 a wavefront for int8 and int4 keys, 860 for
+// values (row norms as well), 1600-2400 for a centroid block; 32768 tokens x 8 heads take
+// 27 us exact, 32-40 us at the int levels, 87-122 us centroid, 24-27 us one-centroid.
+// Four wavefronts per SIMD: the keys need 122 registers, the values spill nine words.
+template <int TENSOR, bool PER_TOKEN>
+__global__ void __launch_bounds__(kThreads, 4) quantize_kernel(const uint16_t *__restrict__ src, int64_t T_src,
                                                             const int8_t *__restrict__ level,
                                                             const int64_t *__restrict__ off, uint8_t *arena,
-                                                            int Hkv, int nblk_cap, int blk0, int tensor,
-                                                            float *cert, int vtok, const int64_t *seq_len) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  EncodeShared &S = *reinterpret_cast<EncodeShared *>(smem);
+                                                            int Hkv, int nblk_cap, int blk0, float *cert,
+                                                            const int64_t *seq_len) {
+  __shared__ enc::Shared<true> sh;
   const int blk = blk0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int64_t u = (int64_t)b * Hkv + h;
   // a sequence's own length bounds its rows; blocks past its end are not encoded
   const int64_t Tb = seq_len ? (seq_len[b] < T_src ? seq_len[b] : T_src) : T_src;
   if ((int64_t)blk * P >= Tb) return;
-  const int lv = level[u * nblk_cap + blk];
-  const bool per_token = tensor == GKV_VALUES && vtok;
-  load_rows(S, src + u * T_src * D, Tb, (int64_t)blk * P);
-  __syncthreads();
-  encode_to(S, arena + off[u * nblk_cap + blk], lv, tensor, per_token);
-  if (cert) {  // error against the exact rows; the value tensor also keeps the row norms
-    __syncthreads();
-    block_cert(S, lv, per_token);
-    if (threadIdx.x == 0) {
-      float *cb = cert + (u * nblk_cap + blk) * 4;
-      if (tensor == GKV_KEYS) {
-        cb[0] = round_up_f32(S.cert[0]);
-      } else {
-        cb[1] = round_up_f32(S.cert[0]);
-        cb[2] = round_up_f32(S.cert[1]);
-        cb[3] = 0.f;
-      }
+  const int lv = __builtin_amdgcn_readfirstlane((int)level[u * nblk_cap + blk]);
+  const enc::Place pl;
+  enc::HalfSrc s;
+  enc::load_rows(s, pl, src + u * T_src * D, Tb, (int64_t)blk * P);
+  double err, nrm;
+  enc::encode_block<TENSOR, PER_TOKEN>(sh, pl, s, arena + off[u * nblk_cap + blk], lv, cert != nullptr, err, nrm);
+  if (cert && threadIdx.x == 0) {  // error against the exact rows; the value tensor also keeps the row norms
+    float *cb = cert + (u * nblk_cap + blk) * 4;
+    if (TENSOR == GKV_KEYS) {
+      cb[0] = round_up_f32(err);
+    } else {
+      cb[1] = round_up_f32(err);
+      cb[2] = round_up_f32(nrm);
+      cb[3] = 0.f;
     }
   }
 }
@@ -381,31 +64,46 @@ struct DemoteJobs {
   int64_t koff[kMaxDemoteJobs], voff[kMaxDemoteJobs];
 };
 
+// Re-encodes the record at `src` (level cur) at `dst` (level to); err as in encode_block.
+template <int TENSOR, bool PER_TOKEN>
+__device__ __forceinline__ void demote_block(unsigned char *smem, const uint8_t *src, uint8_t *dst, int cur, int to,
+                                             bool cert, double &err) {
+  const enc::Place pl;
+  double nrm;
+  if (cur == GKV_EXACT) {
+    enc::HalfSrc s;
+    enc::load_exact<TENSOR>(s, pl, src);
+    enc::encode_block<TENSOR, PER_TOKEN>(*reinterpret_cast<enc::Shared<true> *>(smem), pl, s, dst, to, cert, err, nrm);
+  } else {
+    enc::WideSrc s;
+    enc::load_decoded<TENSOR, PER_TOKEN>(s, pl, src, cur);
+    enc::encode_block<TENSOR, PER_TOKEN>(*reinterpret_cast<enc::Shared<false> *>(smem), pl, s, dst, to, cert, err,
+                                         nrm);
+  }
+}
+
 // Demotion: grid (jobs, 2 tensors).  Reads the current record through the device
 // tables, writes the new record, then points the tables at it.
+template <bool PER_TOKEN>
 __global__ void __launch_bounds__(kThreads) demote_kernel(DemoteJobs jobs, int8_t *level, int64_t *koff,
                                                           int64_t *voff, uint8_t *arena, int Hkv, int nblk_cap,
-                                                          float *cert, int vtok) {
+                                                          float *cert) {
   extern __shared__ __align__(16) unsigned char smem[];
-  EncodeShared &S = *reinterpret_cast<EncodeShared *>(smem);
   const int j = blockIdx.x, tensor = blockIdx.y;
   const int64_t idx = ((int64_t)jobs.b[j] * Hkv + jobs.h[j]) * nblk_cap + jobs.blk[j];
-  const int cur = jobs.cur[j];
+  const int cur = jobs.cur[j], to = jobs.to[j];
   int64_t *offt = tensor == GKV_KEYS ? koff : voff;
   const int64_t dst = tensor == GKV_KEYS ? jobs.koff[j] : jobs.voff[j];
-  const bool per_token = tensor == GKV_VALUES && vtok;
-  load_record(S, arena + offt[idx], cur, tensor, per_token);
-  __syncthreads();
-  encode_to(S, arena + dst, jobs.to[j], tensor, per_token);
-  __syncthreads();
-  if (cert) {  // the error grows by at most the change of the reconstruction
-    block_cert(S, jobs.to[j], per_token);
-    if (threadIdx.x == 0) {
-      float *ce = cert + idx * 4 + (tensor == GKV_KEYS ? 0 : 1);
-      *ce = round_up_f32((double)*ce + S.cert[0]);
-    }
-  }
+  const uint8_t *src = arena + offt[idx];
+  double err;
+  if (tensor == GKV_KEYS) demote_block<GKV_KEYS, false>(smem, src, arena + dst, cur, to, cert != nullptr, err);
+  else demote_block<GKV_VALUES, PER_TOKEN>(smem, src, arena + dst, cur, to, cert != nullptr, err);
+  __syncthreads();  // every thread has read the table entry it is about to change
   if (threadIdx.x == 0) {
+    if (cert) {  // the error grows by at most the change of the reconstruction
+      float *ce = cert + idx * 4 + (tensor == GKV_KEYS ? 0 : 1);
+      *ce = round_up_f32((double)*ce + err);
+    }
     offt[idx] = dst;
     if (tensor == GKV_KEYS) level[idx] = jobs.to[j];
   }
@@ -812,9 +510,14 @@ extern "C" gkv_status gkv_quantize_block(const gkv_cache *c, int32_t which, cons
       }
   }
   dim3 grid(blk_end - blk_begin, c->Hkv, c->B);
-  hipLaunchKernelGGL(quantize_kernel, grid, dim3(kThreads), sizeof(EncodeShared), (hipStream_t)stream, src,
-                     T_src, c->level, which == GKV_KEYS ? c->koff : c->voff, c->arena, c->Hkv, c->nblk_cap,
-                     blk_begin, which, c->cert, c->v_per_token, (const int64_t *)c->seq_len);
+#define GKV_QUANT(t, vt)                                                                                            \
+  hipLaunchKernelGGL((quantize_kernel<t, vt>), grid, dim3(kThreads), 0, (hipStream_t)stream, src, T_src, c->level,  \
+                     t == GKV_KEYS ? c->koff : c->voff, c->arena, c->Hkv, c->nblk_cap, blk_begin, c->cert,          \
+                     (const int64_t *)c->seq_len)
+  if (which == GKV_KEYS) GKV_QUANT(GKV_KEYS, false);
+  else if (c->v_per_token) GKV_QUANT(GKV_VALUES, true);
+  else GKV_QUANT(GKV_VALUES, false);
+#undef GKV_QUANT
   return hip_status();
 }
 
@@ -850,8 +553,14 @@ extern "C" gkv_status gkv_demote(gkv_cache *c, int32_t n, const int32_t *jobs, c
       J.koff[i] = nk[base + i];
       J.voff[i] = nv[base + i];
     }
-    hipLaunchKernelGGL(demote_kernel, dim3(cnt, 2), dim3(kThreads), sizeof(EncodeShared), (hipStream_t)stream, J,
-                       c->level, c->koff, c->voff, c->arena, c->Hkv, c->nblk_cap, c->cert, c->v_per_token);
+    constexpr size_t lds = sizeof(enc::Shared<false>) > sizeof(enc::Shared<true>) ? sizeof(enc::Shared<false>)
+                                                                                   : sizeof(enc::Shared<true>);
+    if (c->v_per_token)
+      hipLaunchKernelGGL(demote_kernel<true>, dim3(cnt, 2), dim3(kThreads), lds, (hipStream_t)stream, J, c->level,
+                         c->koff, c->voff, c->arena, c->Hkv, c->nblk_cap, c->cert);
+    else
+      hipLaunchKernelGGL(demote_kernel<false>, dim3(cnt, 2), dim3(kThreads), lds, (hipStream_t)stream, J, c->level,
+                         c->koff, c->voff, c->arena, c->Hkv, c->nblk_cap, c->cert);
     if (hipGetLastError() != hipSuccess) return GKV_E_HIP;
   }
   for (int i = 0; i < n; ++i)
