@@ -31,8 +31,7 @@ union H8 {
 
 constexpr int kObsWaves = 8;
 constexpr int kObsThreads = 64 * kObsWaves;
-constexpr int kObsBlocksPerWave = 128 / kObsWaves;
-constexpr int kObsChunk = kObsWaves * kObsBlocksPerWave;  // blocks per workgroup
+constexpr int kObsMaxWaveBlocks = 16;  // consecutive blocks of one wavefront (see obs_wave_blocks)
 constexpr int kMaxRows = 512;
 constexpr float kNegInf = -__builtin_huge_valf();
 // A running sum may grow to this before its reference is moved to the block's maximum.
@@ -197,7 +196,7 @@ __device__ __forceinline__ void finish_tile(const f16x (&acc)[2], float sl2, int
   st[0] = r;
 }
 
-// Logits and per-block log-sum-exp.  Each wavefront takes kObsBlocksPerWave blocks
+// Logits and per-block log-sum-exp.  Each wavefront takes `wave_blocks` blocks
 // and, per block, every 32-row tile of the group's queries: 16 MFMAs give the 64 x 32
 // logits, then sum_j exp2(x_j - ref) over the block's visible keys with ref the row's
 // running reference (kept in LDS per wavefront and row with the running sum of
@@ -208,7 +207,7 @@ __device__ __forceinline__ void finish_tile(const f16x (&acc)[2], float sl2, int
 __global__ void __launch_bounds__(kObsThreads) obs_logit_kernel(const uint16_t *__restrict__ q_obs,
                                                                 const uint16_t *__restrict__ k_src, int n_obs,
                                                                 int G, int Hkv, int64_t T, int nblk, int Rpad,
-                                                                float sl2, float *__restrict__ lse,
+                                                                int wave_blocks, float sl2, float *__restrict__ lse,
                                                                 float2 *__restrict__ part) {
   extern __shared__ __align__(16) uint8_t qs[];
   float2 *stats = (float2 *)(qs + Rpad * 256);  // [kObsWaves][Rpad] running (reference, sum)
@@ -230,8 +229,8 @@ __global__ void __launch_bounds__(kObsThreads) obs_logit_kernel(const uint16_t *
   float2 *wst = stats + wv * Rpad + j;
   const uint16_t *kb = k_src + u * T * D;
   const int64_t first_masked = T - n_obs + 1;  // keys at or beyond this are hidden from some row
-  const int blk0 = blockIdx.x * kObsChunk + wv * kObsBlocksPerWave;
-  const int nb = blk0 >= nblk ? 0 : (nblk - blk0 < kObsBlocksPerWave ? nblk - blk0 : kObsBlocksPerWave);
+  const int blk0 = (blockIdx.x * kObsWaves + wv) * wave_blocks;
+  const int nb = __builtin_amdgcn_readfirstlane(blk0 >= nblk ? 0 : (nblk - blk0 < wave_blocks ? nblk - blk0 : wave_blocks));
   const int nt = Rpad / 32;
   const uint8_t *qlane = qs + lane * 16;
   H8 a[2][8];
@@ -390,29 +389,43 @@ __global__ void __launch_bounds__(256) obs_mass_kernel(const float *__restrict__
   }
 }
 
-// Largest ||q|| over the group's observed queries, fp64, channel-ascending sums.
-__global__ void __launch_bounds__(256) query_norm_kernel(const uint16_t *__restrict__ q_obs, int n_obs, int G,
+// Largest ||q|| over the group's observed queries, fp64, channel-ascending sums: one
+// thread per row, its 256 bytes loaded at once (the rows may lie at any 2-byte address),
+// the maximum by shuffles.  Latency bounds it (four heads of 448 rows: 13.3 us with 2-byte
+// loads and one thread's serial maximum, 5.7 us now).
+typedef uint32_t q4 __attribute__((ext_vector_type(4), aligned(2)));
+constexpr int kNormThreads = 512;
+__global__ void __launch_bounds__(kNormThreads) query_norm_kernel(const uint16_t *__restrict__ q_obs, int n_obs, int G,
                                                          int Hkv, double *__restrict__ qn) {
-  __shared__ double best[256];
+  __shared__ double best[kNormThreads / 64];
   const int h = blockIdx.x, b = blockIdx.y;
   const int R = n_obs * G, Hq = Hkv * G;
   double mx = 0.0;
-  for (int r = threadIdx.x; r < R; r += 256) {
+  for (int r = threadIdx.x; r < R; r += kNormThreads) {
     const int qi = r / G, g = r - qi * G;
-    const uint16_t *q = q_obs + (((int64_t)b * n_obs + qi) * Hq + h * G + g) * D;
+    const q4 *q = (const q4 *)(q_obs + (((int64_t)b * n_obs + qi) * Hq + h * G + g) * D);
+    q4 w[D / 8];
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) w[i] = q[i];
     double acc = 0.0;
+#pragma unroll
     for (int d = 0; d < D; ++d) {
-      const double x = (double)__builtin_bit_cast(_Float16, q[d]);
+      const double x = (double)(float)__builtin_bit_cast(_Float16, (uint16_t)(w[d >> 3][(d >> 1) & 3] >> (16 * (d & 1))));
       acc = acc + x * x;
     }
     const double n = __builtin_sqrt(acc);
     mx = n > mx ? n : mx;
   }
-  best[threadIdx.x] = mx;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double t = __shfl_xor(mx, o);
+    mx = t > mx ? t : mx;
+  }
+  if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = mx;
   __syncthreads();
   if (threadIdx.x == 0) {
     double m = 0.0;
-    for (int i = 0; i < 256; ++i) m = best[i] > m ? best[i] : m;
+    for (int i = 0; i < kNormThreads / 64; ++i) m = best[i] > m ? best[i] : m;
     qn[(int64_t)b * Hkv + h] = m;
   }
 }
@@ -490,8 +503,20 @@ __global__ void __launch_bounds__(D) alloc_kernel(const uint16_t *__restrict__ k
 int rows_padded(int R) { return (R + 31) / 32 * 32; }
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
+// Consecutive blocks per wavefront of the logit kernel: 16 (each workgroup then loads the
+// queries once per 128 blocks), halved while that leaves fewer workgroups than compute
+// units; one workgroup fills a compute unit's LDS, so with fewer the chip idles (one 128k
+// sequence of 4 KV heads, 448 rows: 64 workgroups of 16 blocks 201 us, 256 of 4 blocks
+// 88 us).  A constant, not the device's count, so that the workspace's size depends on the shapes alone.
+constexpr int64_t kObsFill = 256;
+int obs_wave_blocks(int64_t units, int nblk) {
+  int w = kObsMaxWaveBlocks;
+  while (w > 1 && units * ((nblk + kObsWaves * w - 1) / (kObsWaves * w)) < kObsFill) w /= 2;
+  return w;
+}
+
 struct ObsLayout {
-  int nblk, R, Rpad, nslice;
+  int nblk, R, Rpad, wave_blocks, nslice;
   int64_t lse, part, rows, total;
 };
 
@@ -501,7 +526,8 @@ ObsLayout obs_layout(int B, int Hkv, int Hq, int64_t T, int n_obs) {
   L.nblk = (int)((T + P - 1) / P);
   L.R = n_obs * (Hq / Hkv);
   L.Rpad = rows_padded(L.R);
-  L.nslice = (L.nblk + kObsChunk - 1) / kObsChunk;
+  L.wave_blocks = obs_wave_blocks(units, L.nblk);
+  L.nslice = (L.nblk + kObsWaves * L.wave_blocks - 1) / (kObsWaves * L.wave_blocks);
   L.lse = 0;
   L.part = align256(units * L.nblk * L.Rpad * 4);
   L.rows = L.part + align256(units * L.nslice * L.Rpad * 8);
@@ -543,7 +569,7 @@ extern "C" gkv_status gkv_observe_mass(const uint16_t *q_obs, int32_t n_obs, con
   const int G = Hq / Hkv;
   const float sl2 = 1.4426950408889634f / sqrtf((float)D);
   hipLaunchKernelGGL(obs_logit_kernel, dim3(L.nslice, Hkv, B), dim3(kObsThreads), L.Rpad * (256 + 8 * kObsWaves), s, q_obs,
-                     k_src, n_obs, G, Hkv, T, L.nblk, L.Rpad, sl2, lse, part);
+                     k_src, n_obs, G, Hkv, T, L.nblk, L.Rpad, L.wave_blocks, sl2, lse, part);
   hipLaunchKernelGGL(obs_row_kernel, dim3((L.R + 3) / 4, Hkv, B), dim3(256), 0, s, part, L.R, L.Rpad, L.nslice, Hkv,
                      rows);
   hipLaunchKernelGGL(obs_mass_kernel, dim3((L.nblk + kMassBlocks - 1) / kMassBlocks, Hkv, B), dim3(256), 0, s, lse,
@@ -555,7 +581,7 @@ extern "C" gkv_status gkv_query_norms(const uint16_t *q_obs, int32_t n_obs, int3
                                       double *qn, void *stream) {
   if (B <= 0 || Hkv <= 0 || Hq <= 0 || Hq % Hkv || Hq / Hkv > 16 || n_obs < 1) return GKV_E_SHAPE;
   if (!q_obs || !qn) return GKV_E_ARG;
-  hipLaunchKernelGGL(query_norm_kernel, dim3(Hkv, B), dim3(256), 0, (hipStream_t)stream, q_obs, n_obs, Hq / Hkv,
+  hipLaunchKernelGGL(query_norm_kernel, dim3(Hkv, B), dim3(kNormThreads), 0, (hipStream_t)stream, q_obs, n_obs, Hq / Hkv,
                      Hkv, qn);
   return hipGetLastError() == hipSuccess ? GKV_OK : GKV_E_HIP;
 }

@@ -168,3 +168,49 @@ def test_observer_128k_full_size_sampled(gpu):
     G = Hq // Hkv
     for b, h in samp:
         _mass_close(got[b, h], oobs.observe_mass(_group(q_obs, b, h, G), ks[b, h]))
+
+
+@pytest.mark.parametrize("cold", [False, True])
+@pytest.mark.parametrize("B,nblk,wave_blocks", [(1, 33, 1), (8, 65, 2), (8, 100, 4), (16, 128, 8), (16, 129, 16)])
+def test_observer_blocks_per_wavefront(gpu, B, nblk, wave_blocks, cold):
+    """Every number of blocks a wavefront takes (the largest of 16, 8, 4, 2, 1 that leaves
+    256 workgroups of 8 wavefronts), with a ragged last block and chunk; 'cold' points the
+    first three blocks away from the queries, so that a wavefront of four or more blocks
+    moves its reference.  Plain fp64 on three (sequence, head) units."""
+    import torch
+    Hkv, n_obs = 8, 6
+    T = 64 * nblk - 5
+    w = 16
+    while w > 1 and B * Hkv * -(-nblk // (8 * w)) < 256:
+        w //= 2
+    assert w == wave_blocks
+    g = torch.Generator(device="cuda").manual_seed(7 * nblk + cold)
+    k = torch.randn((B, Hkv, T, 128), generator=g, device="cuda").half()
+    q = torch.randn((B, n_obs, 2 * Hkv, 128), generator=g, device="cuda").half()
+    if cold:
+        d = torch.full((128,), 1 / np.sqrt(128), device="cuda")
+        q = (q.float() * 0.25 + 4.0 * d).half()
+        k[:, :, :192] = (-192.0 * d).half()
+    got = gpu.observe_mass(q.view(torch.int16), k.view(torch.int16)).cpu().numpy()
+    for b, h in ((0, 0), (B - 1, 3), (B // 2, 7)):
+        x = q[b, :, 2 * h:2 * h + 2].double().reshape(-1, 128) @ k[b, h].double().transpose(0, 1).contiguous() / np.sqrt(128)
+        last = T - n_obs + torch.arange(n_obs, device="cuda").repeat_interleave(2)
+        x.masked_fill_(torch.arange(T, device="cuda")[None, :] > last[:, None], -np.inf)
+        m = torch.nn.functional.pad(torch.softmax(x, -1).mean(0), (0, 5)).view(nblk, 64).sum(-1)
+        _mass_close(got[b, h], m.cpu().numpy())
+
+
+@pytest.mark.parametrize("offset", [0, 1, 3])
+@pytest.mark.parametrize("n_obs,G", [(1, 1), (37, 14), (100, 16)])
+def test_query_norms_rows_and_alignment(gpu, n_obs, G, offset):
+    """More rows than threads, and queries at addresses that are only 2-byte aligned."""
+    import torch
+    g = np.random.default_rng(n_obs)
+    q = (g.standard_normal((2, n_obs, 2 * G, 128)) * 3).astype(np.float16).view(np.int16)
+    buf = torch.zeros(q.size + 8, dtype=torch.int16, device="cuda")
+    dev = buf[offset:offset + q.size].view(q.shape)
+    dev.copy_(torch.from_numpy(q))
+    got = gpu.query_norms(dev, 2).cpu().numpy()
+    for b in range(2):
+        for h in range(2):
+            assert got[b, h] == oobs.query_norm(_group(q.view(np.uint16), b, h, G))
