@@ -64,6 +64,18 @@ __device__ __forceinline__ double row_all_d(double x, F op) {
 
 __device__ __forceinline__ h2 as_h2(uint32_t x) { return __builtin_bit_cast(h2, x); }
 __device__ __forceinline__ uint32_t as_u(h2 x) { return __builtin_bit_cast(uint32_t, x); }
+// Inline assembly's results are not known to the compiler as vector-ALU results, so it adds
+// no wait states before a DPP or permlane instruction that reads them: they pass through
+// here first.
+template <class T>
+__device__ __forceinline__ void settle(T &a) {
+  asm volatile("s_nop 4" : "+v"(a));
+}
+__device__ __forceinline__ void settle(uint32_t &a, uint32_t &b) { asm volatile("s_nop 4" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void settle(uint32_t (&a)[4], uint32_t (&b)[4]) {
+  asm volatile("s_nop 4" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));
+}
+
 // Packed fp16 minimum and maximum as one instruction: a quiet NaN operand is ignored.
 // (The builtins first quiet both operands of each; here the words are quieted once.)
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
@@ -337,6 +349,7 @@ __device__ __forceinline__ void block_cert(Shared<HALF> &sh, const Place &pl, S 
         float N = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) N = s.square_plus(r, e, N);
+        settle(N);
         N = row_sum(N);
         nu[r] = N * (1.f + 0x1p-16f);
         nl = fmaxf(nl, N * (1.f - 0x1p-16f));
@@ -583,9 +596,13 @@ __device__ __forceinline__ void encode_int(Shared<S::kHalf> &sh, const Place &pl
         const uint32_t w0 = pk_quiet(s.w[r][0]), w1 = pk_quiet(s.w[r][1]), w2 = pk_quiet(s.w[r][2]),
                        w3 = pk_quiet(s.w[r][3]);
         uint32_t lo = pk_min(pk_min(w0, w1), pk_min(w2, w3)), hi = pk_max(pk_max(w0, w1), pk_max(w2, w3));
+        settle(lo, hi);
         lo = pk_min(lo, dpp<kXor1>(lo)); hi = pk_max(hi, dpp<kXor1>(hi));
+        settle(lo, hi);
         lo = pk_min(lo, dpp<kXor2>(lo)); hi = pk_max(hi, dpp<kXor2>(hi));
+        settle(lo, hi);
         lo = pk_min(lo, dpp<kHalfMirror>(lo)); hi = pk_max(hi, dpp<kHalfMirror>(hi));
+        settle(lo, hi);
         lo = pk_min(lo, dpp<kMirror>(lo)); hi = pk_max(hi, dpp<kMirror>(hi));
         mn = fmn(h2d((uint16_t)lo), h2d((uint16_t)(lo >> 16)));
         mx = fmx(h2d((uint16_t)hi), h2d((uint16_t)(hi >> 16)));
@@ -611,13 +628,30 @@ __device__ __forceinline__ void encode_int(Shared<S::kHalf> &sh, const Place &pl
     __syncthreads();
   } else {
     if constexpr (S::kHalf) {
-      u4 lo, hi;
+      uint32_t l4[4], h4[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint32_t w0 = pk_quiet(s.w[0][i]), w1 = pk_quiet(s.w[1][i]), w2 = pk_quiet(s.w[2][i]),
                        w3 = pk_quiet(s.w[3][i]);
-        lo[i] = over_kg(pk_min(pk_min(w0, w1), pk_min(w2, w3)), pk_min);
-        hi[i] = over_kg(pk_max(pk_max(w0, w1), pk_max(w2, w3)), pk_max);
+        l4[i] = pk_min(pk_min(w0, w1), pk_min(w2, w3));
+        h4[i] = pk_max(pk_max(w0, w1), pk_max(w2, w3));
+      }
+      settle(l4, h4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {  // lanes l ^ 32
+        const auto x = __builtin_amdgcn_permlane32_swap(l4[i], l4[i], false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(h4[i], h4[i], false, false);
+        l4[i] = pk_min(x[0], x[1]);
+        h4[i] = pk_max(y[0], y[1]);
+      }
+      settle(l4, h4);
+      u4 lo, hi;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {  // lanes l ^ 16
+        const auto x = __builtin_amdgcn_permlane16_swap(l4[i], l4[i], false, false);
+        const auto y = __builtin_amdgcn_permlane16_swap(h4[i], h4[i], false, false);
+        lo[i] = pk_min(x[0], x[1]);
+        hi[i] = pk_max(y[0], y[1]);
       }
       if (pl.kg == 0) {
         q.rh[pl.wave][pl.a][0] = lo;
@@ -985,6 +1019,7 @@ __device__ __forceinline__ void encode_centroid(Shared<S::kHalf> &sh, const Plac
       float n = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) n = s.square_plus(r, e, n);
+      settle(n);
       n = row_sum(n);
       if ((pl.lane & 15) == 0) l.xn[t] = __builtin_amdgcn_sqrtf(n);
     } else {
