@@ -79,7 +79,9 @@ __device__ __forceinline__ f4 mfma16(half4 a, half4 b, f4 c) {
 }
 __device__ __forceinline__ uint32_t andor(uint32_t x, uint32_t m, uint32_t c) { return (x & m) | c; }
 // max(a, b) for non-NaN operands as one v_max_f32: fmaxf adds NaN-quieting copies of
-// its operands.
+// its operands.  The compiler adds no wait states between other instructions and inline
+// assembly, so its operands must not come straight from an MFMA nor its result go straight
+// to a DPP or permlane instruction: those uses take fmaxf.
 __device__ __forceinline__ float vmax(float a, float b) {
   float r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -179,7 +181,13 @@ __device__ __forceinline__ uint32_t opaque(uint32_t c) {
   return r;
 }
 
-// Offset (as fp16 pair, negated) of code pair q.
+// The same for an MFMA operand: the move itself is the compiler's, which knows the wait
+// states between it and the MFMA.
+__device__ __forceinline__ uint32_t opaque_operand(uint32_t c) {
+  asm volatile("" : "+s"(c));
+  return c;
+}
+
 // Offset (as fp16 pair, negated) of key code pair q.
 template <int BITS>
 __device__ __forceinline__ uint32_t neg_off_pair(int q) {
@@ -489,9 +497,9 @@ __device__ __forceinline__ void cert_add(State &st, float pb, float kerr, float 
 // pair lane l with l ^ 32 and l ^ 16.
 __device__ __forceinline__ float wave_max16(float x) {
   const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = vmax(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
   const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return vmax(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 __device__ __forceinline__ float wave_sum16(float x) {
@@ -553,7 +561,7 @@ __device__ __forceinline__ bool tile_softmax(const AttnParams &p, State &st, f4 
     float bm = kNegInf;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (mine & (1u << r)) bm = vmax(bm, S[r]);
+      if (mine & (1u << r)) bm = fmaxf(bm, S[r]);
     alpha = rescale_factor(st, wave_max16(bm) * p.sl2);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -594,8 +602,8 @@ __device__ __forceinline__ bool pair_softmax(const AttnParams &p, State &st, f4 
     float bm = kNegInf;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (mine & (1u << r)) bm = vmax(bm, SA[r]);
-      if (mine & (1u << (4 + r))) bm = vmax(bm, SB[r]);
+      if (mine & (1u << r)) bm = fmaxf(bm, SA[r]);
+      if (mine & (1u << (4 + r))) bm = fmaxf(bm, SB[r]);
     }
     alpha = rescale_factor(st, wave_max16(bm) * p.sl2);
 #pragma unroll
@@ -703,6 +711,13 @@ __device__ __forceinline__ void int_header(IntBlock &ib, const uint8_t *qs, cons
     ib.qh[i] = qB[i] * sK[i].h;
     ib.ql[i] = __builtin_elementwise_fma(qB[i], sK[i].h, -ib.qh[i]);
   }
+  // the offsets of chunk i's code pairs: the same for every i (int8, int4) or by i & 1
+  constexpr int kOffs = BITS == 2 ? 2 : 1;
+  U8 off[kOffs];
+#pragma unroll
+  for (int i = 0; i < kOffs; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) off[i].u[e] = opaque_operand(neg_off_pair<BITS>(4 * i + e));
   f4 c0 = {0, 0, 0, 0};
   if (PACK) {
     const bool lo = (lane & 8) != 0;
@@ -713,22 +728,14 @@ __device__ __forceinline__ void int_header(IntBlock &ib, const uint8_t *qs, cons
       c0 = mfma32(zK[i].h, lo ? zero8 : qB[i], c0);  // the zero-point term once per head
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      U8 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o.u[e] = opaque(neg_off_pair<BITS>(4 * i + e));
-      c0 = mfma32(o.h, ib.qh[i], c0);
-    }
+    for (int i = 0; i < 4; ++i) c0 = mfma32(off[i % kOffs].h, ib.qh[i], c0);
   } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i) c0 = mfma32(zK[i].h, qB[i], c0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      U8 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o.u[e] = opaque(neg_off_pair<BITS>(4 * i + e));
-      c0 = mfma32(o.h, ib.qh[i], c0);
-      c0 = mfma32(o.h, ib.ql[i], c0);
+      c0 = mfma32(off[i % kOffs].h, ib.qh[i], c0);
+      c0 = mfma32(off[i % kOffs].h, ib.ql[i], c0);
     }
   }
   ib.c0 = c0;
@@ -953,7 +960,7 @@ __device__ __forceinline__ void centroid_item(const AttnParams &p, State &st, co
   float bm = kNegInf;
 #pragma unroll
   for (int a = 0; a < 4; ++a)
-    if (used[a] > 0.f) bm = vmax(bm, sc[a]);
+    if (used[a] > 0.f) bm = fmaxf(bm, sc[a]);
   rescale_factor(st, bm * p.sl2);
   float pk[4];
 #pragma unroll
@@ -1121,7 +1128,7 @@ __device__ __forceinline__ void mean_run_item(const AttnParams &p, State &st, co
   for (int r = 0; r < 4; ++r) {
     const int g = 4 * (kg & 1) + r;
     c[r] = (float)((cnt >> (8 * g)) & 255u);  // 0 for blocks >= n
-    if (c[r] > 0.f) bm = vmax(bm, sc[r]);
+    if (c[r] > 0.f) bm = fmaxf(bm, sc[r]);
   }
   rescale_factor(st, wave_max16(bm) * p.sl2);
   _Float16 wh[4];
