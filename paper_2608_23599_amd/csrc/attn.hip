@@ -208,7 +208,8 @@ __device__ __forceinline__ float v_off(int j) {
 
 // ---------------------------------------------------------------- parameters
 constexpr int kTagWords = 12;
-constexpr uint64_t kTagMagic = 0x676b76706c616e31ull;  // marks a tag as written by a dense plan
+constexpr uint64_t kTagMagic = 0x676b76706c616e31ull;   // marks a tag as written by a dense plan
+constexpr uint64_t kTagShort = 0x676b7673686f7274ull;   // by a short dense read (it has no plan to reuse)
 
 struct AttnParams {
   const uint16_t *q;
@@ -254,6 +255,10 @@ __device__ __forceinline__ int64_t unit_T(const AttnParams &p, int64_t u) {
 // every length inside the block (appends that open no block keep the plan).
 __device__ __forceinline__ int64_t plan_T(const AttnParams &p, int64_t u) {
   return (unit_T(p, u) + P - 1) / P * P;
+}
+
+__device__ __forceinline__ uint64_t token_mask(int64_t left) {  // tokens of a block below `left`
+  return left >= P ? ~0ull : (left <= 0 ? 0ull : ((1ull << left) - 1));
 }
 
 constexpr int kSlotBytes = 4096;  // one copy unit
@@ -621,6 +626,11 @@ __device__ __forceinline__ bool pair_softmax(const AttnParams &p, State &st, f4 
 }
 
 __device__ __forceinline__ uint4 lds16(const uint8_t *a) { return *(const uint4 *)a; }
+__device__ __forceinline__ uint4 gld16(const uint8_t *a) {  // a record's bytes, read once
+  typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+  const v4 x = __builtin_nontemporal_load((const v4 *)a);
+  return make_uint4(x[0], x[1], x[2], x[3]);
+}
 
 // The group's queries live in LDS, one 272-byte row per head (padded against bank
 // conflicts); lane (head m, kg) reads its B-operand chunk of MFMA i.
@@ -634,6 +644,19 @@ __device__ __forceinline__ half8 qchunk(const uint8_t *qs, int lane, int i) {
   U8 t;
   t.v = lds16(qs + qrow<PACK>(lane) * kQRow + (32 * i + 8 * (lane >> 4)) * 2);
   return t.h;
+}
+
+// ||q||^2 of this lane's head, for eps_b = ||q|| kerr_b / sqrt(D).
+template <bool PACK>
+__device__ __forceinline__ float query_sq(const uint8_t *qs, int lane) {
+  float qq = 0.f;
+  for (int c8 = 0; c8 < D; c8 += 8) {
+    U8 t;
+    t.v = lds16(qs + qrow<PACK>(lane) * kQRow + c8 * 2);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qq = fmaf((float)t.h[e], (float)t.h[e], qq);
+  }
+  return qq;
 }
 
 // x[lane] + x[lane ^ 8] within each 16-lane row (DPP row rotate by 8).
@@ -795,18 +818,14 @@ __device__ __forceinline__ void tok_sz(const uint8_t *ebuf, int ti, int kg, U4 &
   *(uint2 *)zv.u = *(const uint2 *)(ebuf + 128 + 2 * (16 * ti + 4 * kg));
 }
 
-// One 16-token tile of an int block: key codes at kt, value codes at vt (LDS).  With
+// One 16-token tile of an int block from this lane's key and value code words.  With
 // VTOK (values grouped per token) P is scaled by each token's value scale before the
 // P.V product, and sum P * scale and sum P * zero are kept for the block epilogue.
 template <int BITS, bool PACK, bool VTOK>
-__device__ __forceinline__ void int_tile(const AttnParams &p, State &st, IntBlock &ib, const uint8_t *kt,
-                                         const uint8_t *vt, uint32_t tvalid, const Mag &mg, int lane, int ti,
-                                         const uint8_t *ebuf) {
-  constexpr int NW = Unpack<BITS>::kWords;
+__device__ __forceinline__ void int_tile_words(const AttnParams &p, State &st, IntBlock &ib, const uint32_t *kw,
+                                               const uint32_t *vw, uint32_t tvalid, const Mag &mg, int lane, int ti,
+                                               const uint8_t *ebuf) {
   const int kg = lane >> 4;
-  uint32_t kw[NW], vw[NW];  // value codes read now so that the softmax hides the latency
-  tile_words<BITS>(kt + lane * (4 * BITS), kw);
-  tile_words<BITS>(vt + lane * (4 * BITS), vw);
   const f4 S = int_logits<BITS, PACK>(ib, kw, mg);
   half4 P4;
   float alpha;
@@ -833,22 +852,29 @@ __device__ __forceinline__ void int_tile(const AttnParams &p, State &st, IntBloc
     ib.acc[j] = mfma16(as_h4(Unpack<BITS>::pair(vw, 2 * j, mg), Unpack<BITS>::pair(vw, 2 * j + 1, mg)), PV, ib.acc[j]);
 }
 
-// Two consecutive tiles of an int block (tile B's codes follow tile A's).  P.V runs
-// as one 32-deep MFMA per channel group: the contraction index k = 8 kg + e takes
-// tile A's token 4 kg + e for e < 4 and tile B's token 4 kg + e - 4 for e >= 4, in
-// both operands, so each lane's operands are its own registers of the two tiles.
+// The same with the tile's key codes at kt and value codes at vt (LDS; the value codes are
+// read at once so that the softmax hides the latency).
 template <int BITS, bool PACK, bool VTOK>
-__device__ __forceinline__ void int_tile2(const AttnParams &p, State &st, IntBlock &ib, const uint8_t *kt,
-                                          const uint8_t *vt, uint32_t tvA, uint32_t tvB, const Mag &mg, int lane,
-                                          int ta, int tb, const uint8_t *ebuf) {
+__device__ __forceinline__ void int_tile(const AttnParams &p, State &st, IntBlock &ib, const uint8_t *kt,
+                                         const uint8_t *vt, uint32_t tvalid, const Mag &mg, int lane, int ti,
+                                         const uint8_t *ebuf) {
   constexpr int NW = Unpack<BITS>::kWords;
-  constexpr int TB = 256 * BITS;  // code bytes of one tile and tensor
+  uint32_t kw[NW], vw[NW];
+  tile_words<BITS>(kt + lane * (4 * BITS), kw);
+  tile_words<BITS>(vt + lane * (4 * BITS), vw);
+  int_tile_words<BITS, PACK, VTOK>(p, st, ib, kw, vw, tvalid, mg, lane, ti, ebuf);
+}
+
+// Two tiles of an int block.  P.V runs as one 32-deep MFMA per channel group: the
+// contraction index k = 8 kg + e takes tile A's token 4 kg + e for e < 4 and tile B's
+// token 4 kg + e - 4 for e >= 4, in both operands, so each lane's operands are its own
+// registers of the two tiles.
+template <int BITS, bool PACK, bool VTOK>
+__device__ __forceinline__ void int_tile2_words(const AttnParams &p, State &st, IntBlock &ib, const uint32_t *kwA,
+                                                const uint32_t *kwB, const uint32_t *vwA, const uint32_t *vwB,
+                                                uint32_t tvA, uint32_t tvB, const Mag &mg, int lane, int ta, int tb,
+                                                const uint8_t *ebuf) {
   const int kg = lane >> 4;
-  uint32_t kwA[NW], kwB[NW], vwA[NW], vwB[NW];
-  tile_words<BITS>(kt + lane * (4 * BITS), kwA);
-  tile_words<BITS>(kt + TB + lane * (4 * BITS), kwB);
-  tile_words<BITS>(vt + lane * (4 * BITS), vwA);
-  tile_words<BITS>(vt + TB + lane * (4 * BITS), vwB);
   const f4 SA = int_logits<BITS, PACK>(ib, kwA, mg);
   const f4 SB = int_logits<BITS, PACK>(ib, kwB, mg);
   half8 P8;
@@ -884,6 +910,21 @@ __device__ __forceinline__ void int_tile2(const AttnParams &p, State &st, IntBlo
     a.u[3] = Unpack<BITS>::pair(vwB, 2 * j + 1, mg);
     ib.acc[j] = mfma32(a.h, PV, ib.acc[j]);
   }
+}
+
+// The same with the codes in LDS, tile B's after tile A's.
+template <int BITS, bool PACK, bool VTOK>
+__device__ __forceinline__ void int_tile2(const AttnParams &p, State &st, IntBlock &ib, const uint8_t *kt,
+                                          const uint8_t *vt, uint32_t tvA, uint32_t tvB, const Mag &mg, int lane,
+                                          int ta, int tb, const uint8_t *ebuf) {
+  constexpr int NW = Unpack<BITS>::kWords;
+  constexpr int TB = 256 * BITS;  // code bytes of one tile and tensor
+  uint32_t kwA[NW], kwB[NW], vwA[NW], vwB[NW];
+  tile_words<BITS>(kt + lane * (4 * BITS), kwA);
+  tile_words<BITS>(kt + TB + lane * (4 * BITS), kwB);
+  tile_words<BITS>(vt + lane * (4 * BITS), vwA);
+  tile_words<BITS>(vt + TB + lane * (4 * BITS), vwB);
+  int_tile2_words<BITS, PACK, VTOK>(p, st, ib, kwA, kwB, vwA, vwB, tvA, tvB, mg, lane, ta, tb, ebuf);
 }
 
 // End of an int block: O[d][h] += s_d * (acc - off * sum p) + z_d * sum p,
@@ -925,10 +966,10 @@ __device__ __forceinline__ void int_epilogue(State &st, IntBlock &ib, const uint
   st.l += ib.pb[0];
 }
 
-// Centroid block: one unit with both records (K at +0, V at +2 KB).
+// Centroid block: key record at ip, value record at vp (the ring's unit holds it at +2 KB).
 template <bool PACK, bool CERT>
 __device__ __forceinline__ void centroid_item(const AttnParams &p, State &st, const uint8_t *qs, const uint8_t *ip,
-                                              uint64_t valid, int lane, const float *cb) {
+                                              const uint8_t *vp, uint64_t valid, int lane, const float *cb) {
   const int kg = lane >> 4, m16 = lane & 15;
   // logits of the 4 key centroids: rows 4kg + r of A hold centroid r
   f4 sc = {0, 0, 0, 0};
@@ -939,12 +980,12 @@ __device__ __forceinline__ void centroid_item(const AttnParams &p, State &st, co
     sc = mfma32(a.h, qchunk<PACK>(qs, lane, i), sc);
   }
   const uint32_t *kid = (const uint32_t *)(ip + KC * D * 2);
-  const uint32_t *vid = (const uint32_t *)(ip + 2048 + KC * D * 2);
+  const uint32_t *vid = (const uint32_t *)(vp + KC * D * 2);
   const uint32_t ki = (kid[lane >> 4] >> (2 * (lane & 15))) & 3u;
   const uint32_t vi = (vid[lane >> 4] >> (2 * (lane & 15))) & 3u;
   U8 vc[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) vc[i].v = kg == 0 ? lds16(ip + 2048 + m16 * 64 + 16 * i) : make_uint4(0, 0, 0, 0);
+  for (int i = 0; i < 4; ++i) vc[i].v = kg == 0 ? lds16(vp + m16 * 64 + 16 * i) : make_uint4(0, 0, 0, 0);
   const bool on = (valid >> lane) & 1ull;
   float cnt[4][4], used[4];
 #pragma unroll
@@ -985,12 +1026,12 @@ __device__ __forceinline__ void centroid_item(const AttnParams &p, State &st, co
   if (CERT) cert_add(st, lsum, cb[0], cb[1]);
 }
 
-// One-centroid block: one unit with the key row at +0 and the value row at +2 KB.
+// One-centroid block: key row at ip, value row at vp (the ring's unit holds it at +2 KB).
 // All read tokens share one key and one value, so the block adds one logit per head
 // with weight (tokens read) x exp, and that weight times the value row.
 template <bool PACK, bool CERT>
 __device__ __forceinline__ void mean_item(const AttnParams &p, State &st, const uint8_t *qs, const uint8_t *ip,
-                                          uint64_t valid, int lane, const float *cb) {
+                                          const uint8_t *vp, uint64_t valid, int lane, const float *cb) {
   const int kg = lane >> 4;
   // every row of A is the key row, so each output row holds the logit of the column's head
   f4 sc = {0, 0, 0, 0};
@@ -1006,7 +1047,7 @@ __device__ __forceinline__ void mean_item(const AttnParams &p, State &st, const 
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     U4 v;
-    *(uint2 *)v.u = *(const uint2 *)(ip + 2048 + (16 * j + 4 * kg) * 2);
+    *(uint2 *)v.u = *(const uint2 *)(vp + (16 * j + 4 * kg) * 2);
 #pragma unroll
     for (int r = 0; r < 4; ++r) st.O[j][r] = fmaf(w, (float)v.h[r], st.O[j][r]);
   }
@@ -1095,7 +1136,8 @@ template <bool PACK, bool CERT>
 __device__ __forceinline__ bool centroid_run(const AttnParams &p, State &st, const uint8_t *qs, Pipe &pp,
                                              uint32_t &meta, uint64_t &valid, int lane) {
   do {
-    centroid_item<PACK, CERT>(p, st, qs, pp.template pop<0>(), valid, lane, CERT ? pp.cert + pp.blk * 4 : nullptr);
+    const uint8_t *ip = pp.template pop<0>();
+    centroid_item<PACK, CERT>(p, st, qs, ip, ip + 2048, valid, lane, CERT ? pp.cert + pp.blk * 4 : nullptr);
     pp.release(1);
     if (!pp.template next_item<CERT>(meta, valid)) return false;
   } while (meta_lv(meta) == GKV_CENTROID);
@@ -1174,11 +1216,9 @@ __device__ __forceinline__ bool mean_run(const AttnParams &p, State &st, const u
                                          uint32_t &meta, uint64_t &valid, int lane) {
   do {
     const int n = meta_ntiles(meta) + 1;
-    if (n > 1)
-      mean_run_item<PACK, CERT>(p, st, qs, pp.template pop<0>(), n, valid, lane,
-                                CERT ? pp.cert + pp.blk * 4 : nullptr);
-    else
-      mean_item<PACK, CERT>(p, st, qs, pp.template pop<0>(), valid, lane, CERT ? pp.cert + pp.blk * 4 : nullptr);
+    const uint8_t *ip = pp.template pop<0>();
+    if (n > 1) mean_run_item<PACK, CERT>(p, st, qs, ip, n, valid, lane, CERT ? pp.cert + pp.blk * 4 : nullptr);
+    else mean_item<PACK, CERT>(p, st, qs, ip, ip + 2048, valid, lane, CERT ? pp.cert + pp.blk * 4 : nullptr);
     pp.release(1);
     if (!pp.template next_item<CERT>(meta, valid)) return false;
   } while (meta_lv(meta) == GKV_MEAN);
@@ -1256,16 +1296,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_kernel(AttnParams p) {
   st.l = 0.f;
   st.c1 = st.c2 = st.c3 = 0.f;
   st.es = 0.f;
-  if (CERT) {  // ||q|| of this lane's head, for eps_b = ||q|| kerr_b / sqrt(D)
-    float qq = 0.f;
-    for (int c8 = 0; c8 < D; c8 += 8) {
-      U8 t;
-      t.v = lds16(qs + qrow<PACK>(lane) * kQRow + c8 * 2);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qq = fmaf((float)t.h[e], (float)t.h[e], qq);
-    }
-    st.es = __builtin_sqrtf(qq) * p.sl2;  // sl2 = log2(e) / sqrt(D)
-  }
+  if (CERT) st.es = __builtin_sqrtf(query_sq<PACK>(qs, lane)) * p.sl2;  // sl2 = log2(e) / sqrt(D)
 
   // ---------------- pipelined item loop
   // Items are processed in runs of one level, each run in a loop specialised for
@@ -1327,6 +1358,373 @@ __global__ void __launch_bounds__(kThreads, 2) attn_kernel(AttnParams p) {
       out[g * kPart + 1] = L;
     }
     if (CERT && d < 3) out[g * kPart + D + 2 + d] = cc;
+  }
+}
+
+// ---------------------------------------------------------------- short reads
+// Reads that give each wavefront a block or less (short contexts, Compressed-Quest pages)
+// are bound by latency, not bytes: the planned kernel spends a third of its time there on
+// its plan's and descriptors' round trips and on its ring (issuing a first unit costs it
+// 1300 cycles, a tile pair behind a full ring 600 a unit).  Here a wavefront takes
+// "pieces" of at most two tiles of one block, loads the piece's records straight into
+// registers in MFMA operand order (the packed layout is built for that; scales and zeros
+// pass through LDS) and keeps nothing in flight across pieces: with 16 wavefronts per
+// compute unit the others hide its loads.  No plan kernel, and with all pieces of a (b, KV
+// head) in one workgroup no merge kernel either.
+struct Piece {
+  const uint8_t *kp, *vp;  // records
+  int level, t0;           // level (-1: nothing to read), first tile
+  int blk;                 // block index (certificate)
+  uint64_t valid;          // tokens of the block that are read, within the piece's tiles
+};
+
+// Pieces of a (b, KV head): dense, two per block and per residual pseudo-block; in a
+// Compressed-Quest read one per 16- or 32-token page, two per 64-token page.
+template <bool QUEST, int NT>
+__device__ __forceinline__ Piece piece_at(const AttnParams &p, int64_t u, int64_t Tu, int64_t nblk, int64_t g) {
+  Piece c;
+  int64_t blk;
+  c.level = -1;
+  c.kp = c.vp = nullptr;
+  c.t0 = 0;
+  c.blk = 0;
+  c.valid = 0;
+  bool whole = !QUEST || p.page == 64;  // the pieces of a block cover all of it
+  if (QUEST) {
+    const int tpp = p.page / 16, pshift = p.page == 16 ? 2 : (p.page == 32 ? 1 : 0);
+    const int64_t cur = (Tu - 1) / p.page, slot = tpp == 4 ? g >> 1 : g;
+    int64_t q = cur;
+    if (slot < p.topk) {
+      q = p.pages[u * p.topk + slot];
+      if (q < 0 || q >= cur) return c;
+    }
+    blk = q >> pshift;
+    c.t0 = tpp == 4 ? 2 * (int)(g & 1) : (int)(q & ((1 << pshift) - 1)) * tpp;
+  } else {
+    blk = g >> 1;
+    c.t0 = 2 * (int)(g & 1);
+    if (blk >= nblk) {  // residual rows
+      const int64_t rb = blk - nblk;
+      c.kp = p.res_rows + (u * p.nrb_cap + rb) * (2 * kExactBytes);
+      c.vp = c.kp + kExactBytes;
+      c.level = GKV_EXACT;
+      c.valid = token_mask(p.nres - rb * P);
+    }
+  }
+  if (c.level < 0) {
+    const int64_t i = u * p.nblk_cap + blk;
+    c.blk = (int)blk;
+    c.level = p.level[i];
+    c.kp = p.arena + p.koff[i];
+    c.vp = p.arena + p.voff[i];
+    c.valid = token_mask(Tu - blk * P);
+    if (!QUEST && p.nres) c.valid &= ~p.res_mask[i];
+  }
+  whole &= c.level < GKV_INT2;  // a centroid block's first piece reads all of it, the second nothing
+  if (!whole) c.valid &= (NT == 2 ? 0xFFFFFFFFull : 0xFFFFull) << (16 * c.t0);
+  if (!c.valid || (whole && c.t0)) c.level = -1;
+  return c;
+}
+
+// A lane index whose derived values are not shared between the levels' branches (shared,
+// they are held in registers throughout the loop, and the kernel spills).
+__device__ __forceinline__ int branch_lane(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// One or two exact tiles.
+template <int NT, bool PACK, bool CERT>
+__device__ __forceinline__ void piece_exact(const AttnParams &p, State &st, const uint8_t *qs, const Piece &c,
+                                            int lane) {
+  const int kg = lane >> 4;
+  const uint8_t *kt = c.kp + 4096 * c.t0 + lane * 64, *vt = c.vp + 4096 * c.t0 + lane * 64;
+  const uint32_t tvA = (uint32_t)(c.valid >> (16 * c.t0)) & 0xFFFFu;
+  U8 ka[4], va[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ka[i].v = gld16(kt + 16 * i);
+  f4 SA = {0, 0, 0, 0};
+  if (NT == 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) va[i].v = gld16(vt + 16 * i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) SA = mfma32(ka[i].h, qchunk<PACK>(qs, lane, i), SA);
+    half4 P4;
+    float alpha;
+    tile_softmax(p, st, SA, tvA, kg, P4, alpha);
+    const f4 pb = mfma16(kOnes, P4, f4{0, 0, 0, 0});
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      st.O[j] = mfma16(as_h4(va[j >> 1].u[2 * (j & 1)], va[j >> 1].u[2 * (j & 1) + 1]), P4, st.O[j]);
+    st.l += pb[0];
+    if (CERT) {  // exact rows: no logit or value error
+      st.c2 += pb[0];
+      st.c3 += pb[0];
+    }
+    return;
+  }
+  const uint32_t tvB = (uint32_t)(c.valid >> (16 * c.t0 + 16)) & 0xFFFFu;
+  U8 kb[4], vb[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) kb[i].v = gld16(kt + 4096 + 16 * i);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    va[i].v = gld16(vt + 16 * i);
+    vb[i].v = gld16(vt + 4096 + 16 * i);
+  }
+  f4 SB = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const half8 q = qchunk<PACK>(qs, lane, i);
+    SA = mfma32(ka[i].h, q, SA);
+    SB = mfma32(kb[i].h, q, SB);
+  }
+  half8 P8;
+  float alpha;
+  pair_softmax(p, st, SA, SB, tvA, tvB, kg, P8, alpha);
+  const f4 pb = mfma32(kOnes8, P8, f4{0, 0, 0, 0});
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    U8 a;
+    a.u[0] = va[j >> 1].u[2 * (j & 1)];
+    a.u[1] = va[j >> 1].u[2 * (j & 1) + 1];
+    a.u[2] = vb[j >> 1].u[2 * (j & 1)];
+    a.u[3] = vb[j >> 1].u[2 * (j & 1) + 1];
+    st.O[j] = mfma32(a.h, P8, st.O[j]);
+  }
+  st.l += pb[0];
+  if (CERT) {
+    st.c2 += pb[0];
+    st.c3 += pb[0];
+  }
+}
+
+// This lane's code words of one tile (global memory).
+template <int BITS>
+__device__ __forceinline__ void tile_words_g(const uint8_t *c, uint32_t *w) {
+  if (BITS == 2) {
+    const uint2 a = *(const uint2 *)c;
+    w[0] = a.x; w[1] = a.y;
+  } else {
+#pragma unroll
+    for (int q = 0; q < BITS; q += 4) {
+      const uint4 a = gld16(c + 4 * q);
+      w[q] = a.x; w[q + 1] = a.y; w[q + 2] = a.z; w[q + 3] = a.w;
+    }
+  }
+}
+
+// One or two tiles of an int block; eb: 1 KB of LDS of this wavefront (scales and zeros).
+// A piece's P.V sums go into the output one channel group at a time, so that no block
+// accumulators are held (with them the kernel needed 220 registers).
+template <int BITS, int NT, bool PACK, bool VTOK, bool CERT>
+__device__ __forceinline__ void piece_int(const AttnParams &p, State &st, const uint8_t *qs, uint8_t *eb,
+                                          const Piece &c, int lane, const float *cb) {
+  constexpr int NW = Unpack<BITS>::kWords;
+  constexpr int TB = 256 * BITS;
+  const int kg = lane >> 4;
+  constexpr bool two = NT == 2;
+  const uint2 hk = *(const uint2 *)(c.kp + 8 * lane), hv = *(const uint2 *)(c.vp + 8 * lane);
+  const uint8_t *kc = c.kp + kSZBytes + c.t0 * TB + lane * (4 * BITS);
+  const uint8_t *vc = c.vp + kSZBytes + c.t0 * TB + lane * (4 * BITS);
+  uint32_t kA[NW], vA[NW], kB[NW], vB[NW];
+  tile_words_g<BITS>(kc, kA);
+  if (two) tile_words_g<BITS>(kc + TB, kB);
+  tile_words_g<BITS>(vc, vA);
+  if (two) tile_words_g<BITS>(vc + TB, vB);
+  *(uint2 *)(eb + 8 * lane) = hk;
+  *(uint2 *)(eb + 512 + 8 * lane) = hv;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // every lane's stores, read by all lanes
+  Mag mg;
+  if (BITS != 8) {
+    mg.e1024 = opaque(E1024);
+    mg.e256 = opaque(E256);
+    mg.e64 = opaque(E64);
+    mg.e16 = opaque(E16);
+    mg.e4 = opaque(E4);
+  }
+  IntBlock ib;
+  int_header<BITS, PACK>(ib, qs, eb, lane);
+  const uint32_t tvA = (uint32_t)(c.valid >> (16 * c.t0)) & 0xFFFFu;
+  f4 pb, ps, pz;
+  float alpha;
+  U8 pv;  // the probabilities as P.V takes them: one tile in the first half, or two
+  if (two) {
+    const uint32_t tvB = (uint32_t)(c.valid >> (16 * c.t0 + 16)) & 0xFFFFu;
+    const f4 SA = int_logits<BITS, PACK>(ib, kA, mg), SB = int_logits<BITS, PACK>(ib, kB, mg);
+    pair_softmax(p, st, SA, SB, tvA, tvB, kg, pv.h, alpha);
+    pb = mfma32(kOnes8, pv.h, f4{0, 0, 0, 0});
+  } else {
+    const f4 SA = int_logits<BITS, PACK>(ib, kA, mg);
+    half4 P4;
+    tile_softmax(p, st, SA, tvA, kg, P4, alpha);
+    pb = mfma16(kOnes, P4, f4{0, 0, 0, 0});
+    U4 t;
+    t.h = P4;
+    pv.u[0] = t.u[0];
+    pv.u[1] = t.u[1];
+    pv.u[2] = pv.u[3] = 0;
+  }
+  if (VTOK) {
+    U4 sA, zA, sB, zB;
+    tok_sz(eb + 512, c.t0, kg, sA, zA);
+    sB.u[0] = sB.u[1] = zB.u[0] = zB.u[1] = 0;
+    if (two) tok_sz(eb + 512, c.t0 + 1, kg, sB, zB);
+    U8 s8, z8;
+    s8.u[0] = sA.u[0]; s8.u[1] = sA.u[1]; s8.u[2] = sB.u[0]; s8.u[3] = sB.u[1];
+    z8.u[0] = zA.u[0]; z8.u[1] = zA.u[1]; z8.u[2] = zB.u[0]; z8.u[3] = zB.u[1];
+    pz = mfma32(z8.h, pv.h, f4{0, 0, 0, 0});
+    pv.h = pv.h * s8.h;  // one rounding of the exact fp16 product
+    ps = mfma32(kOnes8, pv.h, f4{0, 0, 0, 0});
+  }
+  const uint8_t *sz = eb + 512 + kg * 64;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {  // channels 16 j + 4 kg + r, as in int_epilogue
+    f4 acc;
+    if (two) {
+      U8 a;
+      a.u[0] = Unpack<BITS>::pair(vA, 2 * j, mg);
+      a.u[1] = Unpack<BITS>::pair(vA, 2 * j + 1, mg);
+      a.u[2] = Unpack<BITS>::pair(vB, 2 * j, mg);
+      a.u[3] = Unpack<BITS>::pair(vB, 2 * j + 1, mg);
+      acc = mfma32(a.h, pv.h, f4{0, 0, 0, 0});
+    } else {
+      acc = mfma16(as_h4(Unpack<BITS>::pair(vA, 2 * j, mg), Unpack<BITS>::pair(vA, 2 * j + 1, mg)),
+                   as_h4(pv.u[0], pv.u[1]), f4{0, 0, 0, 0});
+    }
+    const float off = v_off<BITS>(j);
+    if (VTOK) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) st.O[j][r] += fmaf(-off, ps[r], acc[r]) + pz[r];
+    } else {
+      U4 s4, z4;
+      *(uint2 *)s4.u = *(const uint2 *)(sz + 8 * j);
+      *(uint2 *)z4.u = *(const uint2 *)(sz + 256 + 8 * j);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float x = fmaf(-off, pb[r], acc[r]);
+        st.O[j][r] = fmaf((float)s4.h[r], x, fmaf((float)z4.h[r], pb[r], st.O[j][r]));
+      }
+    }
+  }
+  st.l += pb[0];
+  if (CERT) cert_add(st, pb[0], cb[0], cb[1]);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // eb may be written again
+}
+
+// LDS of a workgroup of short reads: queries and scale/zero buffers, then the merge
+// buffers in the same place.
+template <bool PACK, int WAVES>
+constexpr size_t short_lds() {
+  constexpr size_t GP = PACK ? 8 : 16, merge = (size_t)WAVES * GP * (D + 1) * 4 + 5 * WAVES * GP * 4;
+  constexpr size_t run = 16 * 272 + (size_t)WAVES * 1024;
+  return merge > run ? merge : run;
+}
+
+// Workgroup L of the grid serves (b, KV head) L mod units as its workgroup L / units;
+// NT: tiles of a piece (1 for 16-token pages); wavefront w of the W of a (b, KV head) takes a piece and every W-th after it.  `out`: the result
+// itself when one workgroup holds all pieces, else null (partials as attn_kernel's).
+template <int NT, bool PACK, bool VTOK, bool QUEST, bool CERT, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, QUEST ? 3 : 2) short_kernel(AttnParams p, int64_t npieces, float *out) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  constexpr int GP = PACK ? 8 : 16;
+  const int units = (int)gridDim.x / p.nsplit;
+  const int sidx = (int)blockIdx.x / units;
+  const int64_t u = (int)blockIdx.x % units;
+  const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int kg = lane >> 4, m16 = lane & 15;
+  if (!QUEST && p.cacheable && blockIdx.x == 0 && threadIdx.x == 0) {  // the state this call read
+#pragma unroll
+    for (int i = 0; i < kTagWords; ++i) p.tag[i] = p.key[i];
+  }
+  uint8_t *qs = smem, *eb = smem + 16 * kQRow + wave * 1024;
+  const int qg = threadIdx.x / (D / 8), qc8 = (threadIdx.x % (D / 8)) * 8;
+  uint4 qv = make_uint4(0, 0, 0, 0);
+  if (qg < p.G) qv = *(const uint4 *)(p.q + (u * p.G + qg) * D + qc8);
+  const int64_t Tu = uni64(unit_T(p, u));
+  const int64_t nblk = (Tu + P - 1) / P;
+  // a ragged sequence's own pieces; an empty or retired one has none
+  int64_t np = npieces;
+  if (!QUEST) np = 2 * (nblk + (p.nres + P - 1) / P);
+  if (Tu == 0) np = 0;
+  const int W = p.nsplit * WAVES;
+  // a dense read's workgroups take every nsplit-th piece, so that the exact blocks at the
+  // end, with the most bytes, spread over the chip (in one workgroup they doubled its time)
+  int64_t g = QUEST ? sidx * WAVES + wave : (int64_t)wave * p.nsplit + sidx;
+  Piece c;
+  c.level = -1;
+  if (g < np) c = piece_at<QUEST, NT>(p, u, Tu, nblk, g);
+  if (WAVES == 4 || threadIdx.x < 256) *(uint4 *)(qs + qg * kQRow + qc8 * 2) = qv;
+  __syncthreads();
+  State st;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) st.O[j] = f4{0, 0, 0, 0};
+  st.m = kNegInf;
+  st.l = 0.f;
+  st.c1 = st.c2 = st.c3 = 0.f;
+  st.es = 0.f;
+  if (CERT) st.es = __builtin_sqrtf(query_sq<PACK>(qs, lane)) * p.sl2;
+  while (g < np) {
+    const float *cb = CERT ? p.cert + (u * p.nblk_cap + c.blk) * 4 : nullptr;
+    const int ln = branch_lane(lane);
+    switch (c.level) {
+      case GKV_EXACT: piece_exact<NT, PACK, CERT>(p, st, qs, c, branch_lane(ln)); break;
+      case GKV_INT8: piece_int<8, NT, PACK, VTOK, CERT>(p, st, qs, eb, c, branch_lane(ln), cb); break;
+      case GKV_INT4: piece_int<4, NT, PACK, VTOK, CERT>(p, st, qs, eb, c, branch_lane(ln), cb); break;
+      case GKV_INT2: piece_int<2, NT, PACK, VTOK, CERT>(p, st, qs, eb, c, branch_lane(ln), cb); break;
+      case GKV_CENTROID: centroid_item<PACK, CERT>(p, st, qs, c.kp, c.vp, c.valid, branch_lane(ln), cb); break;
+      case GKV_MEAN: mean_item<PACK, CERT>(p, st, qs, c.kp, c.vp, c.valid, branch_lane(ln), cb); break;
+      default: break;
+    }
+    g += W;
+    if (g < np) c = piece_at<QUEST, NT>(p, u, Tu, nblk, g);
+  }
+  // ---------------- merge the wavefronts
+  __syncthreads();
+  float *so = (float *)smem;  // [WAVES][GP][D + 1]
+  float *sm = so + WAVES * GP * (D + 1), *sl = sm + WAVES * GP, *scs = sl + WAVES * GP;
+  if (m16 < GP) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) so[(wave * GP + m16) * (D + 1) + 16 * j + 4 * kg + r] = st.O[j][r];
+    if (kg == 0) {
+      sm[wave * GP + m16] = st.m;
+      sl[wave * GP + m16] = st.l;
+      if (CERT) {
+        scs[wave * GP + m16] = st.c1;
+        scs[(WAVES + wave) * GP + m16] = st.c2;
+        scs[(2 * WAVES + wave) * GP + m16] = st.c3;
+      }
+    }
+  }
+  __syncthreads();
+  float *part = p.part + (u * p.nsplit + sidx) * (int64_t)p.G * kPart;
+  for (int i = threadIdx.x; i < p.G * D; i += 64 * WAVES) {
+    const int h = i >> 7, d = i & 127;
+    float M = kNegInf;
+#pragma unroll
+    for (int q = 0; q < WAVES; ++q) M = fmaxf(M, sm[q * GP + h]);
+    float L = 0.f, o = 0.f, cc = 0.f;  // cc: certificate sum d (d < 3)
+    if (M > kNegInf) {
+#pragma unroll
+      for (int q = 0; q < WAVES; ++q) {
+        const float a = __builtin_amdgcn_exp2f(sm[q * GP + h] - M);
+        L = fmaf(sl[q * GP + h], a, L);
+        o = fmaf(so[(q * GP + h) * (D + 1) + d], a, o);
+        if (CERT && d < 3) cc = fmaf(scs[(d * WAVES + q) * GP + h], a, cc);
+      }
+    }
+    if (out) {
+      out[(u * p.G + h) * D + d] = L > 0.f ? o * (1.0f / L) : 0.f;
+    } else {
+      part[h * kPart + 2 + d] = o;
+      if (d == 0) {
+        part[h * kPart] = M;
+        part[h * kPart + 1] = L;
+      }
+      if (CERT && d < 3) part[h * kPart + D + 2 + d] = cc;
+    }
   }
 }
 
@@ -1448,10 +1846,6 @@ __device__ __forceinline__ uint32_t balance_cost(int lv, uint64_t va) {
   if (lv == GKV_EXACT) return tiles * kCostExactTile;
   const uint32_t per = lv == 8 ? kCostInt8Tile : (lv == 4 ? kCostInt4Tile : kCostInt2Tile);
   return kCostIntBlock + tiles * per;
-}
-
-__device__ __forceinline__ uint64_t token_mask(int64_t left) {  // tokens of a block below `left`
-  return left >= P ? ~0ull : (left <= 0 ? 0ull : ((1ull << left) - 1));
 }
 
 // Wavefront inclusive scan of a 32-bit value in lane order: DPP row shifts within
@@ -2053,6 +2447,53 @@ static int attn_fast(int nsplit, int64_t units) {
   return (int)(cus / units);
 }
 
+// Short reads (short_kernel): the wavefronts per workgroup and workgroups per (b, KV head),
+// or waves = 0 where the planned kernel runs.
+struct ShortPlan {
+  int waves, nsplit;
+  int64_t pieces;  // per (b, KV head)
+};
+// Eight wavefronts a workgroup (four for pages, which are many and small): sixteen need
+// 128 registers, which spills, and a kernel with scratch took 30 us whatever its work.
+constexpr int kShortDenseWaves = 8, kShortQuestWaves = 4;
+// Pieces per (b, KV head) that one workgroup takes alone: four per wavefront, about 2 us
+// each, against a merge kernel's 3.2 us and its launch (64 pieces of 2048 tokens: 19.4 us
+// alone, 6.4 + 3.2 us over eight workgroups; the planned kernels 1.5 + 9.7 + 3.2 us).
+constexpr int64_t kShortOne = 32;
+// Pieces over all (b, KV head) of a dense short read: beyond, the planned kernel's ring
+// hides the loads better than another round of pieces (16384 tokens x 8 heads, 4096
+// pieces: 12.5 + 4.0 us against 2.0 + 11.5 + 3.9 us planned).
+constexpr int64_t kShortMax = 4096;
+// Bytes of partials of a Compressed-Quest read, whose reads are short at any context
+// (B = 1: 129 pages at 32k 8.7 -> 6.1 us, 257 at 1M 11.0 -> 7.8 us; B = 8, 8256 pages:
+// 21.2 -> 19.7 us); a larger workspace keeps the planned kernel's wavefronts.
+constexpr int64_t kShortPart = 24ll << 20;
+static ShortPlan short_plan(const gkv_cache *c, int32_t topk, int64_t T, int32_t nres) {
+  const int64_t units = (int64_t)c->B * c->Hkv;
+  ShortPlan s = {0, 0, 0};
+  if (topk > 0) {
+    if (nres > 0) return s;  // the residual rows of a page: the planned kernel's lists
+    s.pieces = ((int64_t)topk + 1) * (c->page == 64 ? 2 : 1);
+    const int64_t nsplit = (s.pieces + kShortQuestWaves - 1) / kShortQuestWaves;
+    if (units * nsplit * (c->Hq / c->Hkv) * kPart * 4 > kShortPart) return s;
+    s.waves = kShortQuestWaves;
+    s.nsplit = (int)nsplit;
+    return s;
+  }
+  s.pieces = 2 * ((T + P - 1) / P + (nres + P - 1) / P);
+  if (s.pieces > kShortOne && units * s.pieces > kShortMax) return s;
+  s.waves = kShortDenseWaves;
+  s.nsplit = s.pieces <= kShortOne ? 1 : (int)((s.pieces + s.waves - 1) / s.waves);
+  return s;
+}
+// Workgroups per (b, KV head) of any short read of the cache (the layout's capacity).
+static int short_ncap(const gkv_cache *c, int32_t topk) {
+  if (topk > 0) return short_plan(c, topk, 0, 0).nsplit;
+  const int64_t most = kShortMax / ((int64_t)c->B * c->Hkv);
+  const int64_t pieces = 2 * ((int64_t)c->nblk_cap + (c->nres_cap + P - 1) / P);
+  return (int)((pieces < most ? pieces : most) / kShortDenseWaves) + 1;
+}
+
 // Workspace layout, sized by the cache capacity so that it does not move as T grows:
 // plan tag | partials | wavefront splits (items, units) | visit descriptors | item
 // descriptors | unit descriptors (+512 B: the descriptor copies read whole 512-byte
@@ -2067,12 +2508,14 @@ static AttnLayout attn_layout(const gkv_cache *c, int32_t topk) {
   const int64_t units = (int64_t)c->B * c->Hkv;
   const int G = c->Hq / c->Hkv;
   L.ncap = attn_nsplit(c, topk, (int64_t)c->nblk_cap * P, true);
+  const int sc = short_ncap(c, topk);
+  const int64_t pcap = sc > L.ncap ? sc : L.ncap;  // partials: whichever kernel has more
   // a dense plan's lists; Compressed-Quest reads keep theirs in LDS
   L.vcap = topk > 0 ? 0 : (int64_t)c->nblk_cap + (c->nres_cap + P - 1) / P;
   L.icap = 4 * L.vcap;  // at most 4 items per visit
   L.ucap = 8 * L.vcap;  // at most 8 units per visit (an exact block)
   L.part = 256;  // the plan tag (kTagWords words) comes first
-  L.split = L.part + align256(units * L.ncap * G * kPart * 4);
+  L.split = L.part + align256(units * pcap * G * kPart * 4);
   L.visits = L.split + align256(units * 2 * ((int64_t)L.ncap * kWaves + 1) * 4);
   L.plan = L.visits + align256(units * L.vcap * (int64_t)sizeof(VisitDesc));
   L.units = L.plan + align256(units * L.icap * (int64_t)sizeof(ItemDesc));
@@ -2085,7 +2528,7 @@ int64_t gkv_attn_workspace(const gkv_cache *c, int32_t topk) { return attn_layou
 // Checks the call and fills the kernel parameters (q and out may be null for the
 // stages that do not use them).
 static gkv_status attn_setup(const uint16_t *q, const gkv_cache *c, const int32_t *pages, int32_t topk, void *ws,
-                             int64_t ws_bytes, AttnParams &p) {
+                             int64_t ws_bytes, AttnParams &p, ShortPlan &sp) {
   gkv_status st = gkv_validate_cache(c);
   if (st) return st;
   if (!ws) return GKV_E_ARG;
@@ -2132,7 +2575,8 @@ static gkv_status attn_setup(const uint16_t *q, const gkv_cache *c, const int32_
   p.page = c->page ? c->page : 16;
   p.cert = c->cert;
   p.bound = nullptr;
-  p.nsplit = attn_nsplit(c, topk, c->T, false);
+  sp = short_plan(c, topk, c->T, c->nres);
+  p.nsplit = sp.waves ? sp.nsplit : attn_nsplit(c, topk, c->T, false);
   p.fast = attn_fast(p.nsplit, (int64_t)c->B * c->Hkv);
   p.sl2 = 1.4426950408889634f / sqrtf((float)D);
   // the key of the planned state: a dense plan depends on the tables (version stamp
@@ -2149,11 +2593,35 @@ static gkv_status attn_setup(const uint16_t *q, const gkv_cache *c, const int32_
                                    (uint64_t)(uintptr_t)c->res_mask,
                                    (uint64_t)(uintptr_t)c->res_rows,
                                    (uint64_t)(uint32_t)c->B | ((uint64_t)(uint32_t)c->Hkv << 32),
-                                   kTagMagic};
+                                   sp.waves ? kTagShort : kTagMagic};
   for (int i = 0; i < kTagWords; ++i) p.key[i] = key[i];
   return GKV_OK;
 }
 
+// The short read: `out` for the result itself (one workgroup per (b, KV head)), else the
+// partials.
+static void launch_short(const AttnParams &p, const ShortPlan &sp, const gkv_cache *c, float *out, hipStream_t s) {
+  const dim3 grid(sp.nsplit * c->Hkv * c->B), blk(64 * sp.waves);
+  const bool pack = p.G <= 8, vtok = c->v_per_token != 0;
+#define GKV_SHORT(nt, a, b, q, ce, w) \
+  hipLaunchKernelGGL((short_kernel<nt, a, b, q, ce, w>), grid, blk, (short_lds<a, w>()), s, p, sp.pieces, out)
+#define GKV_SHORT_READ(a, b)                                                               \
+  do {                                                                                     \
+    if (p.pages && p.page == 16) GKV_SHORT(1, a, b, true, false, kShortQuestWaves);        \
+    else if (p.pages) GKV_SHORT(2, a, b, true, false, kShortQuestWaves);                   \
+    else if (p.bound) GKV_SHORT(2, a, b, false, true, kShortDenseWaves);                   \
+    else GKV_SHORT(2, a, b, false, false, kShortDenseWaves);                               \
+  } while (0)
+  if (pack) {
+    if (vtok) GKV_SHORT_READ(true, true);
+    else GKV_SHORT_READ(true, false);
+  } else {
+    if (vtok) GKV_SHORT_READ(false, true);
+    else GKV_SHORT_READ(false, false);
+  }
+#undef GKV_SHORT_READ
+#undef GKV_SHORT
+}
 static void launch_plan(const AttnParams &p, const gkv_cache *c, hipStream_t s) {
   if (p.pages) return;  // Compressed-Quest reads list their pages in the attention kernel
   // one workgroup per 256 visits of a (b, KV head), at most 8
@@ -2206,9 +2674,10 @@ static void launch_merge(const AttnParams &p, const gkv_cache *c, float *out, hi
 extern "C" gkv_status gkv_attn_plan(const gkv_cache *c, const int32_t *pages, int32_t topk, void *ws, int64_t ws_bytes,
                                     void *stream) {
   AttnParams p;
-  const gkv_status st = attn_setup(nullptr, c, pages, topk, ws, ws_bytes, p);
+  ShortPlan sp;
+  const gkv_status st = attn_setup(nullptr, c, pages, topk, ws, ws_bytes, p, sp);
   if (st) return st;
-  launch_plan(p, c, (hipStream_t)stream);
+  if (!sp.waves) launch_plan(p, c, (hipStream_t)stream);  // a short read has no plan
   return hipGetLastError() == hipSuccess ? GKV_OK : GKV_E_HIP;
 }
 
@@ -2216,9 +2685,11 @@ extern "C" gkv_status gkv_attn_partials(const uint16_t *q, const gkv_cache *c, c
                                         void *ws, int64_t ws_bytes, void *stream) {
   if (!q) return GKV_E_ARG;
   AttnParams p;
-  const gkv_status st = attn_setup(q, c, pages, topk, ws, ws_bytes, p);
+  ShortPlan sp;
+  const gkv_status st = attn_setup(q, c, pages, topk, ws, ws_bytes, p, sp);
   if (st) return st;
-  launch_partials(p, c, (hipStream_t)stream);
+  if (sp.waves) launch_short(p, sp, c, nullptr, (hipStream_t)stream);
+  else launch_partials(p, c, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? GKV_OK : GKV_E_HIP;
 }
 
@@ -2226,7 +2697,8 @@ extern "C" gkv_status gkv_attn_merge(const gkv_cache *c, const int32_t *pages, i
                                      int64_t ws_bytes, void *stream) {
   if (!out) return GKV_E_ARG;
   AttnParams p;
-  const gkv_status st = attn_setup(nullptr, c, pages, topk, ws, ws_bytes, p);
+  ShortPlan sp;
+  const gkv_status st = attn_setup(nullptr, c, pages, topk, ws, ws_bytes, p, sp);
   if (st) return st;
   launch_merge(p, c, out, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? GKV_OK : GKV_E_HIP;
@@ -2236,12 +2708,17 @@ extern "C" gkv_status gkv_graded_decode_attn_bound(const uint16_t *q, const gkv_
                                                    void *ws, int64_t ws_bytes, void *stream) {
   if (!q || !out || !bound || !c || !c->cert) return GKV_E_ARG;
   AttnParams p;
-  const gkv_status st = attn_setup(q, c, nullptr, 0, ws, ws_bytes, p);
+  ShortPlan sp;
+  const gkv_status st = attn_setup(q, c, nullptr, 0, ws, ws_bytes, p, sp);
   if (st) return st;
   p.bound = bound;
   const hipStream_t s = (hipStream_t)stream;
-  launch_plan(p, c, s);
-  launch_partials(p, c, s);
+  if (sp.waves) {
+    launch_short(p, sp, c, nullptr, s);  // the merge forms the bound
+  } else {
+    launch_plan(p, c, s);
+    launch_partials(p, c, s);
+  }
   launch_merge(p, c, out, s);
   return hipGetLastError() == hipSuccess ? GKV_OK : GKV_E_HIP;
 }
@@ -2250,12 +2727,18 @@ extern "C" gkv_status gkv_graded_decode_attn(const uint16_t *q, const gkv_cache 
                                              int32_t topk, float *out, void *ws, int64_t ws_bytes, void *stream) {
   if (!q || !out) return GKV_E_ARG;
   AttnParams p;
-  const gkv_status st = attn_setup(q, c, pages, topk, ws, ws_bytes, p);
+  ShortPlan sp;
+  const gkv_status st = attn_setup(q, c, pages, topk, ws, ws_bytes, p, sp);
   if (st) return st;
   const hipStream_t s = (hipStream_t)stream;
-  launch_plan(p, c, s);
-  launch_partials(p, c, s);
-  launch_merge(p, c, out, s);
+  if (sp.waves) {
+    launch_short(p, sp, c, sp.nsplit == 1 ? out : nullptr, s);
+    if (sp.nsplit > 1) launch_merge(p, c, out, s);
+  } else {
+    launch_plan(p, c, s);
+    launch_partials(p, c, s);
+    launch_merge(p, c, out, s);
+  }
   return hipGetLastError() == hipSuccess ? GKV_OK : GKV_E_HIP;
 }
 
