@@ -124,12 +124,16 @@ def _np_ptr(a):
     return ctypes.c_void_p(a.ctypes.data)
 
 
+# Pointers and streams go to the library as plain integers, which the declared argument
+# types take as they are: the ctypes objects and torch's Stream object of every call cost
+# more of its host time than a kernel launch does.
 def _dptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The raw handle of the current device's current stream."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def block_bytes(level):
