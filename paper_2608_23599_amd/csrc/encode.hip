@@ -312,55 +312,127 @@ __global__ void __launch_bounds__(kThreads) boxes_kernel(const uint16_t *__restr
 // product and a sum; the square and each addition round once.  grid (nblk, Hkv, B),
 // 64 threads.
 //
-// Staged words: chunk ck (32 codes, 4 tokens x 8 channels) holds `wpc` words; the 16
-// chunks of one four-token group c = ck >> 4 are contiguous, and group c starts at
-// word c * kRdGroup (4 words of padding after each group's 16 * wpc), so that the
-// lanes of the 16 groups, which read the same word of their own group, fall in
-// different banks.
-constexpr int kRdGroup = 16 * 8 + 4;
+// Staged words: chunk ck (32 codes, 4 tokens x 8 channels) holds `wpc` words, at most
+// four: an int8 record is staged one half of its channels at a time, an exact one a
+// quarter.  The 16 chunks of one four-token group c = ck >> 4 are contiguous, and group c
+// starts at word c * kRdGroup (4 words of padding after the 16 * 4), so that the lanes of
+// the 16 groups, which read the same word of their own group, fall in different banks.
+//
+// Vector instructions (1135 a wavefront at the graded ladder, conversions at half rate)
+// and HBM each take more than half of the time; loads in flight and wavefronts overlap
+// them.  The whole selection of 131072 tokens (8 sequences, 4 KV heads, 2% kept) took
+// 349.5 us with each lane loading its own 256-byte row, 341.4 us with the rows in 64-byte
+// quarters turned in LDS and an int8 record staged whole (11 wavefronts a compute unit),
+// 338.3 us as it is (12 wavefronts); with one quarter in flight (15 wavefronts) 353.3 us,
+// with the registers held to 128 (15 wavefronts, row loads spilled) 425.8 us.
+constexpr int kRdGroup = 16 * 4 + 4;
 
 struct RdShared {
   uint32_t w[16 * kRdGroup];  // staged record words (also the centroids as fp64)
   double2 sz[D];              // per channel: (scale, zero); the one-centroid value in .x
+  uint32_t tr[P * 16];        // one quarter of the source rows
 };
 
 __device__ __forceinline__ double h2d(uint32_t bits16) {
   return (double)(float)__builtin_bit_cast(_Float16, (uint16_t)bits16);
 }
 
-// Stage the 256 chunks of a record, wpc words of each (chunk ck's at word
-// ck * src_wpc + src_off of `src`), into the group layout: wpc 16-byte pieces a lane.
-__device__ __forceinline__ void rd_stage(uint32_t *w, const uint8_t *src, int wpc, int src_wpc, int src_off,
-                                         int lane) {
-  const int gw = 16 * wpc;  // words of one group
-  for (int i = 0; i < wpc; ++i) {
+// Stage the 256 chunks of a record, WPC words of each (chunk ck's at word
+// ck * src_wpc + src_off of `src`), into the group layout: WPC 16-byte pieces a lane.
+template <int WPC>
+__device__ __forceinline__ void rd_load(bw4 (&x)[WPC], const uint8_t *src, int src_wpc, int src_off, int lane) {
+#pragma unroll
+  for (int i = 0; i < WPC; ++i) {
     const int w0 = (i * 64 + lane) * 4;  // staged word index without padding
-    const int ck = w0 / wpc, k = w0 % wpc;
-    const bw4 x = __builtin_nontemporal_load((const bw4 *)(src + ((int64_t)ck * src_wpc + src_off + k) * 4));
-    *(bw4 *)(w + (w0 / gw) * kRdGroup + w0 % gw) = x;
+    x[i] = __builtin_nontemporal_load((const bw4 *)(src + ((int64_t)(w0 / WPC) * src_wpc + src_off + w0 % WPC) * 4));
+  }
+}
+template <int WPC>
+__device__ __forceinline__ void rd_store(uint32_t *w, const bw4 (&x)[WPC], int lane) {
+  constexpr int gw = 16 * WPC;  // words of one group
+#pragma unroll
+  for (int i = 0; i < WPC; ++i) {
+    const int w0 = (i * 64 + lane) * 4;
+    *(bw4 *)(w + (w0 / gw) * kRdGroup + w0 % gw) = x[i];
   }
 }
 
 // This lane's code of channel d = 16 j + m (token t: group c = t >> 2, tq = t & 3):
-// code n = 4 j + tq of chunk 16 c + m, at bit pos[j & 3] = code_pos(BITS, n) of its word.
+// code n = 4 j + tq of chunk 16 c + m, at bit pos[j & 3] = code_pos(BITS, n) of its word
+// (an int8 chunk's words 0..3 or 4..7 are the staged ones).
 template <int BITS>
 __device__ __forceinline__ uint32_t rd_code(const uint32_t *wl, int j, int m, const int (&pos)[4]) {
-  const uint32_t word = wl[m * BITS + 4 * j / (32 / BITS)];
+  constexpr int wpc = BITS < 4 ? BITS : 4;
+  const uint32_t word = wl[m * wpc + 4 * j / (32 / BITS) % wpc];
   return __builtin_amdgcn_ubfe(word, (uint32_t)pos[j & 3], BITS);
 }
 
-// e += (v_d - v_hat(d))^2 over the channels, ascending.
-template <class F>
-__device__ __forceinline__ void rd_chain(double &e, const uint32_t (&vr)[64], F vhat) {
+// The source rows of a block, read in 64-byte row quarters: load r of quarter q takes
+// channels 32 q .. of rows 16 r .. 16 r + 15, four lanes a row.  Two quarters are in flight;
+// a quarter goes through LDS to the lanes that own its rows.
+struct RdRows {
+  const uint16_t *at[4];
+  bw4 x[2][4];
+  __device__ __forceinline__ void load(int q) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    const double v = h2d(vr[d >> 1] >> (16 * (d & 1)));
-    const double diff = v - vhat(d);
+    for (int r = 0; r < 4; ++r) x[q & 1][r] = *(const bw4 *)(at[r] + 32 * q);
+  }
+};
+
+// e += (v_d - v_hat(d))^2 over the channels of quarter q, ascending.  Row t's piece p
+// lies at slot p ^ (t >> 2 & 3) of its 64 bytes: the sixteen lanes that a 16-byte access
+// serves at once fall on distinct banks, written as well as read.
+template <class F>
+__device__ __forceinline__ void rd_quarter(double &e, uint32_t *tr, RdRows &rows, int q, int lane, F vhat) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int t = 16 * r + (lane >> 2);
+    *(bw4 *)(tr + 16 * t + 4 * ((lane & 3) ^ (t >> 2 & 3))) = rows.x[q & 1][r];
+  }
+  if (q < 2) rows.load(q + 2);
+  __syncthreads();
+  uint32_t vr[16];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const bw4 y = *(const bw4 *)(tr + 16 * lane + 4 * (p ^ (lane >> 2 & 3)));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) vr[4 * p + k] = y[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    const double v = h2d(vr[i >> 1] >> (16 * (i & 1)));
+    const double diff = v - vhat(32 * q + i);
     const double sq = diff * diff;
     e = e + sq;
-    // LDS reads are not hoisted past 16 channels (else the unrolled chain keeps the
-    // reads of many more channels in registers)
-    if ((d & 15) == 15) asm volatile("" ::: "memory");
+    // neither LDS reads nor conversions are hoisted past 8 channels (else the unrolled
+    // chain keeps those of many more channels in registers)
+    if ((i & 7) == 7) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+template <class F>
+__device__ __forceinline__ void rd_chain(double &e, uint32_t *tr, RdRows &rows, int lane, F vhat) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) rd_quarter(e, tr, rows, q, lane, vhat);
+}
+
+// The chain over a record staged in 4 / Q parts of Q row quarters.
+template <int Q, class F>
+__device__ __forceinline__ void rd_chain_parts(double &e, RdShared &S, RdRows &rows, const uint8_t *src,
+                                               int src_wpc, int lane, F vhat) {
+#pragma unroll
+  for (int q0 = 0; q0 < 4; q0 += Q) {
+    bw4 x[4];
+    rd_load(x, src, src_wpc, 4 * (q0 / Q), lane);
+    rd_store(S.w, x, lane);
+    __syncthreads();
+#pragma unroll
+    for (int q = q0; q < q0 + Q; ++q) rd_quarter(e, S.tr, rows, q, lane, vhat);
+    __syncthreads();
   }
 }
 
@@ -376,48 +448,31 @@ __global__ void __launch_bounds__(64) rd_score_kernel(const uint16_t *__restrict
   const int64_t u = (int64_t)b * Hkv + h;
   const int64_t ti = u * nblk_cap + blk;
   const int64_t tok = (int64_t)blk * P + lane;
-  const int64_t tr = tok < T ? tok : T - 1;  // rows past T are read as the last row, not stored
   const int lv = level[ti];
   const uint8_t *rec = arena + voff[ti];
 
-  // this token's source row, 16 bytes at a time (cached loads: the eight loads of
-  // one 128-byte line by the same lane find it in the cache)
-  uint32_t vr[64];
-  const bw4 *row = (const bw4 *)(v_src + (u * T + tr) * D);
+  RdRows rows;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const bw4 x = row[i];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) vr[4 * i + k] = x[k];
+  for (int r = 0; r < 4; ++r) {
+    const int64_t t = (int64_t)blk * P + 16 * r + (lane >> 2);  // rows past T: the last row, not stored
+    rows.at[r] = v_src + (u * T + (t < T ? t : T - 1)) * D + 8 * (lane & 3);
   }
-  const double a = (double)mass[u * T + tr];
+  rows.load(0);
+  rows.load(1);
+  const double a = (double)mass[u * T + (tok < T ? tok : T - 1)];
 
   double e = 0.0;
   const uint32_t *wl = S.w + c * kRdGroup;
   if (lv == GKV_EXACT) {  // chunk ck: 64 B; channels 16 j + m of token 4 c + tq at half 4 j + tq of chunk 16 c + m
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      if (hf) __syncthreads();
-      rd_stage(S.w, rec, 8, 16, 8 * hf, lane);
-      __syncthreads();
-      const uint32_t *wh = wl + (tq >> 1);
-      const int sh = 16 * (tq & 1);
-#pragma unroll
-      for (int d = 64 * hf; d < 64 * hf + 64; ++d) {
-        const int j = (d >> 4) - 4 * hf, m = d & 15;
-        const double v = h2d(vr[d >> 1] >> (16 * (d & 1)));
-        const double diff = v - h2d(wh[m * 8 + 2 * j] >> sh);
-        const double sq = diff * diff;
-        e = e + sq;
-        if ((d & 15) == 15) asm volatile("" ::: "memory");
-      }
-    }
+    const uint32_t *wh = wl + (tq >> 1);
+    const int sh = 16 * (tq & 1);
+    rd_chain_parts<1>(e, S, rows, rec, 16, lane, [&](int d) { return h2d(wh[(d & 15) * 4 + 2 * (d >> 4 & 1)] >> sh); });
   } else if (lv == GKV_MEAN || lv == GKV_CENTROID) {
     const uint16_t *cc = (const uint16_t *)rec;
     if (lv == GKV_MEAN) {
       for (int d = lane; d < D; d += 64) S.sz[d].x = h2d(cc[d]);
       __syncthreads();
-      rd_chain(e, vr, [&](int d) { return S.sz[d].x; });
+      rd_chain(e, S.tr, rows, lane, [&](int d) { return S.sz[d].x; });
     } else {
       double *cent = (double *)S.w;  // [KC][D + 1]
       for (int i = lane; i < KC * D; i += 64) {
@@ -427,7 +482,7 @@ __global__ void __launch_bounds__(64) rd_score_kernel(const uint16_t *__restrict
       const int id = (rec[KC * D * 2 + (lane >> 2)] >> (2 * (lane & 3))) & 3;
       __syncthreads();
       const double *ct = cent + id * (D + 1);
-      rd_chain(e, vr, [&](int d) { return ct[d]; });
+      rd_chain(e, S.tr, rows, lane, [&](int d) { return ct[d]; });
     }
   } else {  // int8 / int4 / int2: (scale, zero) per channel or per token, then the codes
     const uint16_t *sz = (const uint16_t *)rec;
@@ -442,21 +497,29 @@ __global__ void __launch_bounds__(64) rd_score_kernel(const uint16_t *__restrict
 #pragma unroll
     for (int r = 0; r < 4; ++r) pos[r] = code_pos(lv, 4 * r + tq);
     const uint8_t *codes = rec + kSZBytes;
-    if (lv == GKV_INT8) rd_stage(S.w, codes, 8, 8, 0, lane);
-    else if (lv == GKV_INT4) rd_stage(S.w, codes, 4, 4, 0, lane);
-    else rd_stage(S.w, codes, 2, 2, 0, lane);
-    __syncthreads();
-#define GKV_RD_INT(BITS)                                                                                   \
-  if (vtok)                                                                                                \
-    rd_chain(e, vr, [&](int d) { return __builtin_fma((double)rd_code<BITS>(wl, d >> 4, d & 15, pos), s, z); }); \
-  else                                                                                                     \
-    rd_chain(e, vr, [&](int d) {                                                                           \
-      const double2 g = S.sz[d];                                                                           \
+#define GKV_RD_INT(BITS, CHAIN, ...)                                                                        \
+  if (vtok)                                                                                                 \
+    CHAIN(e, __VA_ARGS__, [&](int d) { return __builtin_fma((double)rd_code<BITS>(wl, d >> 4, d & 15, pos), s, z); }); \
+  else                                                                                                      \
+    CHAIN(e, __VA_ARGS__, [&](int d) {                                                                      \
+      const double2 g = S.sz[d];                                                                            \
       return __builtin_fma((double)rd_code<BITS>(wl, d >> 4, d & 15, pos), g.x, g.y);                       \
     })
-    if (lv == GKV_INT8) GKV_RD_INT(8);
-    else if (lv == GKV_INT4) GKV_RD_INT(4);
-    else GKV_RD_INT(2);
+    if (lv == GKV_INT8) {
+      GKV_RD_INT(8, rd_chain_parts<2>, S, rows, codes, 8, lane);
+    } else if (lv == GKV_INT4) {
+      bw4 x[4];
+      rd_load(x, codes, 4, 0, lane);
+      rd_store(S.w, x, lane);
+      __syncthreads();
+      GKV_RD_INT(4, rd_chain, S.tr, rows, lane);
+    } else {
+      bw4 x[2];
+      rd_load(x, codes, 2, 0, lane);
+      rd_store(S.w, x, lane);
+      __syncthreads();
+      GKV_RD_INT(2, rd_chain, S.tr, rows, lane);
+    }
 #undef GKV_RD_INT
   }
   if (tok < T) {
