@@ -268,7 +268,9 @@ constexpr int kChunk = 32;        // descriptors per 512-byte chunk
 // per wavefront: ring | unit-descriptor chunks (2 x 512) | item-descriptor chunks
 // (2 x 512) | value scale/zero of the current int block (512)
 constexpr int kWaveLds = kRing + 4 * 512 + 512;
-constexpr int kMaxWaves = 1024;   // wavefronts per (b, KV head)
+constexpr int kMaxWaves = 1024;   // wavefronts per (b, KV head) of the planned kernel
+// workgroups per (b, KV head) of either kernel: the merge's LDS holds a weight of each
+constexpr int kMaxSplits = kMaxWaves / kWaves;
 // partial per workgroup and head: m, l, o[D], then the certificate sums c1, c2, c3
 constexpr int kPart = D + 5;
 
@@ -1735,7 +1737,7 @@ __global__ void __launch_bounds__(64 * WAVES, QUEST ? 3 : 2) short_kernel(AttnPa
 __global__ void __launch_bounds__(D) merge_kernel(const float *part, float *out, int nsplit, int G, float *bound,
                                                   const float *cert, int nblk_cap, int nblk,
                                                   const int64_t *seq_len, int Hkv) {
-  __shared__ float sa[kMaxWaves / kWaves], sl[kMaxWaves / kWaves];
+  __shared__ float sa[kMaxSplits], sl[kMaxSplits];  // nsplit <= kMaxSplits (attn_split)
   __shared__ float sinv, svm[D];
   const int g = blockIdx.x, d = threadIdx.x;
   const int64_t u = blockIdx.y;
@@ -2475,6 +2477,7 @@ static ShortPlan short_plan(const gkv_cache *c, int32_t topk, int64_t T, int32_t
     if (nres > 0) return s;  // the residual rows of a page: the planned kernel's lists
     s.pieces = ((int64_t)topk + 1) * (c->page == 64 ? 2 : 1);
     const int64_t nsplit = (s.pieces + kShortQuestWaves - 1) / kShortQuestWaves;
+    if (nsplit > kMaxSplits) return s;  // more than the merge holds
     if (units * nsplit * (c->Hq / c->Hkv) * kPart * 4 > kShortPart) return s;
     s.waves = kShortQuestWaves;
     s.nsplit = (int)nsplit;
@@ -2482,8 +2485,10 @@ static ShortPlan short_plan(const gkv_cache *c, int32_t topk, int64_t T, int32_t
   }
   s.pieces = 2 * ((T + P - 1) / P + (nres + P - 1) / P);
   if (s.pieces > kShortOne && units * s.pieces > kShortMax) return s;
+  const int64_t nsplit = s.pieces <= kShortOne ? 1 : (s.pieces + kShortDenseWaves - 1) / kShortDenseWaves;
+  if (nsplit > kMaxSplits) return s;  // one long sequence of one KV head: more than the merge holds
   s.waves = kShortDenseWaves;
-  s.nsplit = s.pieces <= kShortOne ? 1 : (int)((s.pieces + s.waves - 1) / s.waves);
+  s.nsplit = (int)nsplit;
   return s;
 }
 // Workgroups per (b, KV head) of any short read of the cache (the layout's capacity).
@@ -2491,7 +2496,8 @@ static int short_ncap(const gkv_cache *c, int32_t topk) {
   if (topk > 0) return short_plan(c, topk, 0, 0).nsplit;
   const int64_t most = kShortMax / ((int64_t)c->B * c->Hkv);
   const int64_t pieces = 2 * ((int64_t)c->nblk_cap + (c->nres_cap + P - 1) / P);
-  return (int)((pieces < most ? pieces : most) / kShortDenseWaves) + 1;
+  const int64_t n = (pieces < most ? pieces : most) / kShortDenseWaves + 1;
+  return (int)(n < kMaxSplits ? n : kMaxSplits);
 }
 
 // Workspace layout, sized by the cache capacity so that it does not move as T grows:
@@ -2525,6 +2531,37 @@ static AttnLayout attn_layout(const gkv_cache *c, int32_t topk) {
 
 int64_t gkv_attn_workspace(const gkv_cache *c, int32_t topk) { return attn_layout(c, topk).total; }
 
+// The kernel of a read (sp.waves: the short one) and its workgroups per (b, KV head); sizes
+// the call refuses, among them a split that the merge could not hold.
+static gkv_status attn_split(const gkv_cache *c, int32_t topk, const AttnLayout &L, ShortPlan &sp, int &nsplit) {
+  if (topk > 0) {  // the wavefronts that share the read pages, at most kMaxWaves
+    const int ppw = quest_pages_per_wave(c->page, c->nres_cap > 0);
+    if ((topk + 1 + ppw - 1) / ppw > kMaxWaves) return GKV_E_UNSUPPORTED;
+  }
+  if (L.vcap > 32767) return GKV_E_UNSUPPORTED;  // the dense plan's packed prefix sums
+  sp = short_plan(c, topk, c->T, c->nres);
+  nsplit = sp.waves ? sp.nsplit : attn_nsplit(c, topk, c->T, false);
+  return nsplit <= kMaxSplits ? GKV_OK : GKV_E_UNSUPPORTED;
+}
+
+// The split and the workspace ranges of a read, for checks on a host without a GPU:
+// out = {wavefronts of a short read's workgroup or 0, workgroups per (b, KV head), their
+// limit, first and last byte + 1 of the partials, of the dense plan's lists, workspace
+// bytes}.
+extern "C" gkv_status gkv_attn_extents(const gkv_cache *c, int32_t topk, int64_t *out) {
+  if (topk > 0 && c->page != 16 && c->page != 32 && c->page != 64) return GKV_E_ARG;
+  const AttnLayout L = attn_layout(c, topk);
+  ShortPlan sp;
+  int nsplit = 0;
+  const gkv_status st = attn_split(c, topk, L, sp, nsplit);
+  if (st) return st;
+  const int64_t v[8] = {sp.waves, nsplit, kMaxSplits, L.part,
+                        L.part + (int64_t)c->B * c->Hkv * nsplit * (c->Hq / c->Hkv) * kPart * 4,
+                        L.split, topk > 0 ? L.split : L.total - 512, L.total};
+  for (int i = 0; i < 8; ++i) out[i] = v[i];
+  return GKV_OK;
+}
+
 // Checks the call and fills the kernel parameters (q and out may be null for the
 // stages that do not use them).
 static gkv_status attn_setup(const uint16_t *q, const gkv_cache *c, const int32_t *pages, int32_t topk, void *ws,
@@ -2539,12 +2576,9 @@ static gkv_status attn_setup(const uint16_t *q, const gkv_cache *c, const int32_
   } else {
     topk = 0;
   }
-  if (topk > 0) {  // the wavefronts that share the read pages, at most kMaxWaves
-    const int ppw = quest_pages_per_wave(c->page, c->nres_cap > 0);
-    if ((topk + 1 + ppw - 1) / ppw > kMaxWaves) return GKV_E_UNSUPPORTED;
-  }
   const AttnLayout L = attn_layout(c, topk);
-  if (L.vcap > 32767) return GKV_E_UNSUPPORTED;  // the dense plan's packed prefix sums
+  const gkv_status sr = attn_split(c, topk, L, sp, p.nsplit);
+  if (sr) return sr;
   if (ws_bytes < L.total) return GKV_E_WORKSPACE;
   p.q = q;
   p.level = c->level;
@@ -2575,8 +2609,6 @@ static gkv_status attn_setup(const uint16_t *q, const gkv_cache *c, const int32_
   p.page = c->page ? c->page : 16;
   p.cert = c->cert;
   p.bound = nullptr;
-  sp = short_plan(c, topk, c->T, c->nres);
-  p.nsplit = sp.waves ? sp.nsplit : attn_nsplit(c, topk, c->T, false);
   p.fast = attn_fast(p.nsplit, (int64_t)c->B * c->Hkv);
   p.sl2 = 1.4426950408889634f / sqrtf((float)D);
   // the key of the planned state: a dense plan depends on the tables (version stamp

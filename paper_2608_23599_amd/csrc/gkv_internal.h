@@ -151,6 +151,9 @@ inline int64_t seq_tokens(const gkv_cache *c, int b) { return c->seq_len_host ? 
 // Compute units of the current device (cached per device; attn.hip).
 int gkv_device_cus();
 
+// The split and workspace ranges of an attention read (attn.hip).
+extern "C" gkv_status gkv_attn_extents(const gkv_cache *c, int32_t topk, int64_t *out);
+
 // Sets c->version to a new process-wide unique stamp (host.cpp); every call that
 // changes the block tables, T or nres calls it on success.
 void gkv_stamp(gkv_cache *c);

@@ -1,0 +1,73 @@
+"""The attention read's split over workgroups and its workspace ranges, on the host: over
+the accepted shapes neither kernel makes more workgroups per (sequence, KV head) than the
+merge kernel's LDS holds, and the partials stay inside the workspace."""
+import ctypes
+import itertools
+
+import numpy as np
+import pytest
+
+PLANNED = 0
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2608_23599_amd import binding
+    return binding
+
+
+def extents(B, batch, kv, group, T, cap=None, nres=0, nres_cap=0, page=0, topk=0):
+    """gkv_attn_extents of a cache of these sizes (the call reads no table), or its error."""
+    c = B.CacheStruct()
+    c.B, c.Hkv, c.Hq, c.D, c.T = batch, kv, kv * group, 128, T
+    c.nblk_cap = cap or -(-T // 64)
+    c.nres, c.nres_cap, c.page = nres, max(nres, nres_cap), page
+    out = (ctypes.c_int64 * 8)()
+    st = B.lib.gkv_attn_extents(ctypes.byref(c), ctypes.c_int32(topk), out)
+    if st != 0:
+        return st
+    return dict(zip(("waves", "nsplit", "limit", "part", "part_end", "lists", "lists_end", "total"), out))
+
+
+def _dense_shapes():
+    tokens = [1, 64, 65, 1024, 1025, 2048, 16384, 16385, 32768, 60000, 65535, 65536, 65537, 70001, 98304, 131072,
+              131073, 1 << 20, 2097024]
+    for batch, kv, group, T in itertools.product((1, 2, 3, 4, 8, 64), (1, 2, 4, 8), (1, 4, 16), tokens):
+        nb = -(-T // 64)
+        for nres in {0, 1, T // 50, T // 10}:
+            for cap in (nb, nb + 2048):
+                if cap + -(-nres // 64) <= 32767:
+                    yield dict(batch=batch, kv=kv, group=group, T=T, cap=cap, nres=nres)
+
+
+def _quest_shapes():
+    topks = [1, 2, 3, 30, 31, 128, 256, 510, 511, 512, 600, 1022, 1023, 1024, 1025, 2000, 2047, 2048, 4095, 8000, 8191]
+    for batch, kv, group, page, topk, nres_cap in itertools.product((1, 2, 8, 33), (1, 4, 8), (1, 4, 16),
+                                                                    (16, 32, 64), topks, (0, 100)):
+        for nres in {0, nres_cap}:
+            yield dict(batch=batch, kv=kv, group=group, T=1 << 20, nres=nres, nres_cap=nres_cap, page=page, topk=topk)
+
+
+@pytest.mark.parametrize("shapes", [_dense_shapes, _quest_shapes])
+def test_splits_fit_the_merge_and_the_workspace(B, shapes):
+    seen = set()
+    for s in shapes():
+        e = extents(B, **s)
+        if not isinstance(e, dict):
+            assert e == -6 and s.get("topk"), (s, e)  # more read tiles than the call accepts
+            continue
+        seen.add(e["waves"] == PLANNED)
+        assert 1 <= e["nsplit"] <= e["limit"] == 256, (s, e)
+        assert e["part"] >= 256 and e["part_end"] <= e["total"], (s, e)
+    assert seen == {True, False}  # both kernels are among them
+
+
+def test_splits_at_the_merge_limit(B):
+    """256 workgroups are the most a read is split into; one more goes to the planned kernel."""
+    for e in (extents(B, 1, 1, 16, 65536), extents(B, 1, 1, 4, 900 * 64, nres=124 * 64),
+              extents(B, 1, 1, 4, 1 << 20, page=16, topk=1023), extents(B, 1, 1, 4, 1 << 20, page=64, topk=511)):
+        assert e["waves"] != PLANNED and e["nsplit"] == 256, e
+    for e in (extents(B, 1, 1, 16, 65537), extents(B, 1, 1, 16, 131072), extents(B, 1, 1, 4, 900 * 64, nres=124 * 64 + 1),
+              extents(B, 1, 1, 4, 1 << 20, page=16, topk=1024), extents(B, 1, 8, 4, 1 << 20, page=32, topk=1024),
+              extents(B, 1, 1, 4, 1 << 20, page=64, topk=512)):
+        assert e["waves"] == PLANNED and e["nsplit"] <= 256, e

@@ -85,3 +85,45 @@ def test_short_reads_of_ragged_batches(gpu, lens):
                 continue
             uc = ocache.UnitCache(ks[b, h, :t], vs[b, h, :t], olad.ladder("tiny", t))
             assert max_err(got, uc.decode_dense(q_group(q, b, h, 4))) <= TOL
+
+
+# 65536 tokens of one unit are 256 workgroups' pieces, the most the merge holds; one token
+# more, or residual pseudo-blocks past 1024 blocks in all, go to the planned kernel
+@pytest.mark.parametrize("T,Hq,nres", [(65536, 4, 0), (65537, 16, 0), (131072, 4, 0), (900 * 64, 4, 124 * 64),
+                                       (900 * 64, 4, 124 * 64 + 1)])
+def test_one_long_unit_at_the_merge_limit(gpu, T, Hq, nres):
+    import torch
+    ks, vs = kv_all(74, 1, 1, T)
+    lv = olad.ladder("tiny", T)
+    cache = gpu.GradedCache.build(ks, vs, Hq=Hq, levels=lv, nres_cap=nres)
+    uc = ocache.UnitCache(ks[0, 0], vs[0, 0], lv)
+    if nres:
+        mass = synth.mass_unit(74, 0, 0, T)[None, None].astype(np.float32)
+        cache.rd_residual_select(ks, vs, mass, nres)
+        uc.select_residual(ks[0, 0], vs[0, 0], mass[0, 0], nres)
+    q = synth.queries(74, 1, Hq)
+    out = cache.decode(q)
+    assert torch.equal(out, cache.decode(q)) and torch.equal(out, _staged(gpu, cache, q))
+    with_bound, bound = cache.decode_bound(q)
+    assert max_err(out[0].cpu().numpy(), uc.decode_dense(q[0])) <= TOL
+    assert max_err(with_bound[0].cpu().numpy(), uc.decode_dense(q[0])) <= TOL
+    want = uc.certificate(q[0])
+    assert np.all(np.abs(bound[0].cpu().numpy() - want) <= 2e-3 * want + 1e-6)
+
+
+# 1024 pieces of a unit's pages are 256 workgroups
+@pytest.mark.parametrize("page,topk", [(16, 1023), (16, 1024), (32, 1024), (64, 511), (64, 512)])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (32, 8)])
+def test_many_pages_at_the_merge_limit(gpu, page, topk, Hq, Hkv):
+    T = page * (topk + 40) + 5
+    G = Hq // Hkv
+    ks, vs = kv_all(75, 1, Hkv, T)
+    lv = olad.ladder("tiny", T)
+    cache = gpu.GradedCache.build(ks, vs, Hq=Hq, levels=lv, page=page)
+    q = synth.queries(75, 1, Hq)
+    pages = cache.quest_select(q, topk)
+    out = cache.decode(q, pages=pages).cpu().numpy()
+    for h in {0, Hkv - 1}:
+        uc = ocache.UnitCache(ks[0, h], vs[0, h], lv)
+        ref = uc.decode_quest(q_group(q, 0, h, G), pages[0, h].cpu().numpy(), page)
+        assert max_err(out[0, h * G:(h + 1) * G], ref) <= TOL
