@@ -318,9 +318,10 @@ gkv_status gkv_graded_decode_attn(const uint16_t *q, const gkv_cache *c, const i
  * leaves a tag of the planned state (version, block count, nres, table addresses,
  * split) in the workspace; the plan kernel of a later dense call with the same
  * workspace and an identical tag exits at once and the attention reuses the plan.
- * The check runs on the device, so a captured graph replays it correctly.
- * Compressed-Quest calls always plan (their pages change with every query) and
- * invalidate the tag. */
+ * The check runs on the device, so a captured graph replays it correctly.  Reads that
+ * leave no plan (Compressed-Quest reads, whose pages change with every query, and dense
+ * reads of short contexts) leave no tag that a plan kernel would take for its own, so
+ * calls of both kinds, and of several caches, may share one workspace in stream order. */
 
 /* gkv_graded_decode_attn for callers that cannot allocate or pass a workspace (code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation):

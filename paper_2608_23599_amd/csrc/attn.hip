@@ -242,6 +242,19 @@ struct AttnParams {
   uint64_t key[kTagWords];
 };
 
+// The workspace's tag after a read: its key, or (keyed false) no valid one.  Every attention
+// launch leaves one or the other, since its partials may lie where an earlier call's
+// layout has its plan (vector stores; read by later calls' plan kernels).
+__device__ __forceinline__ void leave_tag(const AttnParams &p, bool keyed) {
+  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  if (!keyed) {
+    p.tag[0] = 0;  // a key's version is never 0
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < kTagWords; ++i) p.tag[i] = p.key[i];
+}
+
 // Tokens of (b, KV head) u: its sequence's length, 0 for a retired sequence.
 __device__ __forceinline__ int64_t unit_T(const AttnParams &p, int64_t u) {
   if (!p.seq_len) return p.T;
@@ -1243,12 +1256,9 @@ __global__ void __launch_bounds__(kThreads, 2) attn_kernel(AttnParams p) {
   const int kg = lane >> 4, m16 = lane & 15;
   const int64_t u = (int64_t)b * p.Hkv + h;
   const int W = p.nsplit * kWaves, w = sidx * kWaves + wave;
-  if (p.cacheable && blockIdx.x == 0 && threadIdx.x == 0) {
-    // the plan kernel of this call has finished: the workspace now holds the plan of
-    // this key (vector stores; read by later calls' plan kernels)
-#pragma unroll
-    for (int i = 0; i < kTagWords; ++i) p.tag[i] = p.key[i];
-  }
+  // the plan kernel of this call has finished: the workspace now holds the plan of this
+  // key; a Compressed-Quest read's partials may have overwritten a plan
+  leave_tag(p, !QUEST && p.cacheable);
 
   // the group's queries (rows of absent heads are zero): one 16-byte piece per thread,
   // loaded here and stored to LDS once the wavefront's lists are set up, so that the
@@ -1635,10 +1645,7 @@ __global__ void __launch_bounds__(64 * WAVES, QUEST ? 3 : 2) short_kernel(AttnPa
   const int64_t u = (int)blockIdx.x % units;
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int kg = lane >> 4, m16 = lane & 15;
-  if (!QUEST && p.cacheable && blockIdx.x == 0 && threadIdx.x == 0) {  // the state this call read
-#pragma unroll
-    for (int i = 0; i < kTagWords; ++i) p.tag[i] = p.key[i];
-  }
+  leave_tag(p, !QUEST && p.cacheable);  // the state this call read; no plan is left either way
   uint8_t *qs = smem, *eb = smem + 16 * kQRow + wave * 1024;
   const int qg = threadIdx.x / (D / 8), qc8 = (threadIdx.x % (D / 8)) * 8;
   uint4 qv = make_uint4(0, 0, 0, 0);

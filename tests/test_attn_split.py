@@ -71,3 +71,14 @@ def test_splits_at_the_merge_limit(B):
               extents(B, 1, 1, 4, 1 << 20, page=16, topk=1024), extents(B, 1, 8, 4, 1 << 20, page=32, topk=1024),
               extents(B, 1, 1, 4, 1 << 20, page=64, topk=512)):
         assert e["waves"] == PLANNED and e["nsplit"] <= 256, e
+
+
+def test_short_partials_may_reach_another_layouts_plan(B):
+    """Calls that share a workspace have layouts of their own: a sparse read's partials can
+    lie where a dense read keeps its plan (the reason why no read without a plan of its own
+    leaves a plan's tag valid)."""
+    for batch, kv, T, topk in ((8, 8, 131072, 128), (8, 8, 16384, 128), (4, 4, 10000, 200)):
+        d = extents(B, batch, kv, 4, T, page=16)
+        s = extents(B, batch, kv, 4, T, page=16, topk=topk)
+        assert d["waves"] == PLANNED and d["part_end"] <= d["lists"] <= d["lists_end"] <= d["total"]
+        assert s["waves"] != PLANNED and d["lists"] < s["part_end"] <= s["total"]
