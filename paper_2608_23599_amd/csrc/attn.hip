@@ -2510,7 +2510,9 @@ static int short_ncap(const gkv_cache *c, int32_t topk) {
 // Workspace layout, sized by the cache capacity so that it does not move as T grows:
 // plan tag | partials | wavefront splits (items, units) | visit descriptors | item
 // descriptors | unit descriptors (+512 B: the descriptor copies read whole 512-byte
-// chunks).
+// chunks).  A short read uses the tag and its own partials only, which may be more than the
+// planned kernel's: they run on over the plan, so that no layout grows for them while the
+// plan is the larger (a short read leaves no valid plan tag).
 struct AttnLayout {
   int64_t part, split, visits, plan, units, total, vcap, icap, ucap;
   int ncap;
@@ -2521,18 +2523,18 @@ static AttnLayout attn_layout(const gkv_cache *c, int32_t topk) {
   const int64_t units = (int64_t)c->B * c->Hkv;
   const int G = c->Hq / c->Hkv;
   L.ncap = attn_nsplit(c, topk, (int64_t)c->nblk_cap * P, true);
-  const int sc = short_ncap(c, topk);
-  const int64_t pcap = sc > L.ncap ? sc : L.ncap;  // partials: whichever kernel has more
   // a dense plan's lists; Compressed-Quest reads keep theirs in LDS
   L.vcap = topk > 0 ? 0 : (int64_t)c->nblk_cap + (c->nres_cap + P - 1) / P;
   L.icap = 4 * L.vcap;  // at most 4 items per visit
   L.ucap = 8 * L.vcap;  // at most 8 units per visit (an exact block)
   L.part = 256;  // the plan tag (kTagWords words) comes first
-  L.split = L.part + align256(units * pcap * G * kPart * 4);
+  L.split = L.part + align256(units * L.ncap * G * kPart * 4);
   L.visits = L.split + align256(units * 2 * ((int64_t)L.ncap * kWaves + 1) * 4);
   L.plan = L.visits + align256(units * L.vcap * (int64_t)sizeof(VisitDesc));
   L.units = L.plan + align256(units * L.icap * (int64_t)sizeof(ItemDesc));
   L.total = L.units + units * L.ucap * (int64_t)sizeof(UnitDesc) + 512;
+  const int64_t shorts = L.part + units * short_ncap(c, topk) * G * kPart * 4;
+  if (shorts > L.total) L.total = shorts;
   return L;
 }
 
@@ -2553,7 +2555,7 @@ static gkv_status attn_split(const gkv_cache *c, int32_t topk, const AttnLayout 
 
 // The split and the workspace ranges of a read, for checks on a host without a GPU:
 // out = {wavefronts of a short read's workgroup or 0, workgroups per (b, KV head), their
-// limit, first and last byte + 1 of the partials, of the dense plan's lists, workspace
+// limit, first and last byte + 1 of the partials, of the planned kernel's lists, workspace
 // bytes}.
 extern "C" gkv_status gkv_attn_extents(const gkv_cache *c, int32_t topk, int64_t *out) {
   if (topk > 0 && c->page != 16 && c->page != 32 && c->page != 64) return GKV_E_ARG;
@@ -2564,7 +2566,7 @@ extern "C" gkv_status gkv_attn_extents(const gkv_cache *c, int32_t topk, int64_t
   if (st) return st;
   const int64_t v[8] = {sp.waves, nsplit, kMaxSplits, L.part,
                         L.part + (int64_t)c->B * c->Hkv * nsplit * (c->Hq / c->Hkv) * kPart * 4,
-                        L.split, topk > 0 ? L.split : L.total - 512, L.total};
+                        L.split, L.units + (int64_t)c->B * c->Hkv * L.ucap * (int64_t)sizeof(UnitDesc), L.total};
   for (int i = 0; i < 8; ++i) out[i] = v[i];
   return GKV_OK;
 }

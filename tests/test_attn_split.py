@@ -59,6 +59,10 @@ def test_splits_fit_the_merge_and_the_workspace(B, shapes):
         seen.add(e["waves"] == PLANNED)
         assert 1 <= e["nsplit"] <= e["limit"] == 256, (s, e)
         assert e["part"] >= 256 and e["part_end"] <= e["total"], (s, e)
+        assert e["lists_end"] <= e["total"] and (e["waves"] != PLANNED or e["part_end"] <= e["lists"]), (s, e)
+        # the planned kernel's layout that fits the library's array (32 MiB) is not refused
+        # for the short read's partials
+        assert e["total"] <= max(e["lists_end"] + 512, 32 << 20), (s, e)
     assert seen == {True, False}  # both kernels are among them
 
 
@@ -82,3 +86,27 @@ def test_short_partials_may_reach_another_layouts_plan(B):
         s = extents(B, batch, kv, 4, T, page=16, topk=topk)
         assert d["waves"] == PLANNED and d["part_end"] <= d["lists"] <= d["lists_end"] <= d["total"]
         assert s["waves"] != PLANNED and d["lists"] < s["part_end"] <= s["total"]
+
+
+def test_dense_workspace_is_the_planned_kernels(B):
+    """The dense workspace of a cache whose lists outweigh the short read's partials: the
+    tag, the planned kernel's partials and splits, and 32 + 4 * 16 + 8 * 16 bytes per visit."""
+    for batch, kv, group, T, nres in ((8, 4, 7, 131072, 2621), (8, 8, 4, 131072, 0), (4, 4, 4, 140000, 0),
+                                      (2, 2, 16, 65536, 1000)):
+        units, visits = batch * kv, -(-T // 64) + -(-nres // 64)
+        e = extents(B, batch, kv, group, T, nres=nres)
+        ncap = -(-min(2048 // units, visits) // 4)
+        lists = 256 + -(-units * ncap * group * 133 * 4 // 256) * 256
+        assert e["lists"] == lists, e
+        up = lambda x: -(-x // 256) * 256
+        want = (lists + up(units * 2 * (4 * ncap + 1) * 4) + up(units * visits * 32) + up(units * visits * 64) +
+                units * visits * 128 + 512)
+        assert e["total"] == want, (e, want)
+
+
+def test_noalloc_array_takes_the_largest_planned_layout(B):
+    """The longest dense read whose planned layout fits the array's 32 MiB is not refused."""
+    units, group = 64, 16
+    T = max(t for t in range(64 * 1900, 64 * 2100, 64)
+            if extents(B, 8, 8, group, t)["lists_end"] + 512 <= 32 << 20)
+    assert extents(B, 8, 8, group, T)["total"] <= 32 << 20
