@@ -263,6 +263,7 @@ gkv_status gkv_quantize_block(const gkv_cache *c, int32_t which, const uint16_t 
  * / new_voff_host[i] and updating the device and host level / offset tables.
  * Every job must lower the level (GKV_E_NOT_MONOTONE otherwise; nothing is
  * enqueued then).  A block its sequence does not fill stays exact (GKV_E_SHAPE).
+ * A new record may lie over its own tensor's old one (a demotion in place).
  * The old slots are free once the stream has passed this call. */
 gkv_status gkv_demote(gkv_cache *c, int32_t n, const int32_t *jobs_host, const int8_t *to_level_host,
                       const int64_t *new_koff_host, const int64_t *new_voff_host, void *stream);

@@ -65,18 +65,27 @@ struct DemoteJobs {
 };
 
 // Re-encodes the record at `src` (level cur) at `dst` (level to); err as in encode_block.
+// The new record may lie over the old one: no wavefront writes before every one has read
+// its part (the groups of a token are one wavefront's, so the per-token encoder would
+// otherwise write its scales without a barrier).
 template <int TENSOR, bool PER_TOKEN>
 __device__ __forceinline__ void demote_block(unsigned char *smem, const uint8_t *src, uint8_t *dst, int cur, int to,
                                              bool cert, double &err) {
   const enc::Place pl;
+  const auto loaded = [] {  // a barrier alone does not wait for loads in flight
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
   double nrm;
   if (cur == GKV_EXACT) {
     enc::HalfSrc s;
     enc::load_exact<TENSOR>(s, pl, src);
+    loaded();
     enc::encode_block<TENSOR, PER_TOKEN>(*reinterpret_cast<enc::Shared<true> *>(smem), pl, s, dst, to, cert, err, nrm);
   } else {
     enc::WideSrc s;
     enc::load_decoded<TENSOR, PER_TOKEN>(s, pl, src, cur);
+    loaded();
     enc::encode_block<TENSOR, PER_TOKEN>(*reinterpret_cast<enc::Shared<false> *>(smem), pl, s, dst, to, cert, err,
                                          nrm);
   }

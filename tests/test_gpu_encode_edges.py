@@ -90,3 +90,28 @@ def test_demotion_edges_match_oracle(gpu, chain, per_token):
         for i in range(n):
             for t in (0, 1):
                 compare_record(cache, uc, 0, 0, i, t)
+
+
+@pytest.mark.parametrize("per_token", (False, True))
+@pytest.mark.parametrize("chain", ((8, 4, 2, 1, 0), (2, 1), (4, 0)))
+def test_demotion_in_place(gpu, chain, per_token):
+    """The new record at its old record's offset: the same bytes as in a slot of its own."""
+    import ctypes
+    k, v = _tensors(200 + sum(chain) + per_token)
+    k, v = np.tile(k, (1, 1, 7, 1)), np.tile(v, (1, 1, 7, 1))  # several workgroups on a compute unit
+    n = k.shape[2] // P
+    apart = gpu.GradedCache.build(k, v, Hq=1, levels=np.full(n, 16, np.int8), v_per_token=per_token,
+                                  slack={lv: n for lv in chain})
+    inplace = gpu.GradedCache.build(k, v, Hq=1, levels=np.full(n, 16, np.int8), v_per_token=per_token)
+    jobs = np.array([(0, 0, i) for i in range(n)], np.int32)
+    ko, vo = inplace.koff_host[0, 0].copy(), inplace.voff_host[0, 0].copy()
+    for lv in chain:
+        to = np.full(n, lv, np.int8)
+        apart.demote([tuple(j) for j in jobs], to)
+        st = gpu._demote(ctypes.byref(inplace.c), n, gpu._np_ptr(jobs), gpu._np_ptr(to), gpu._np_ptr(ko),
+                         gpu._np_ptr(vo), gpu._stream())
+        assert st == 0
+        for i in range(n):
+            for t in (0, 1):
+                assert inplace.record_bytes(0, 0, i, t) == apart.record_bytes(0, 0, i, t), (lv, KINDS[i % len(KINDS)], t)
+    assert np.array_equal(inplace.cert.cpu().numpy(), apart.cert.cpu().numpy())
