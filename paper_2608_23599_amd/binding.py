@@ -131,9 +131,16 @@ def _dptr(t):
     return t.data_ptr() if t is not None else None
 
 
+# The lookup without a Stream object is not part of torch's public interface: where a torch
+# has none, the public call stands in.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     """The raw handle of the current device's current stream."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def block_bytes(level):

@@ -1320,3 +1320,12 @@ def test_layers_step_with_sequences_of_different_lengths(gpu):
             assert all(a.pool.used(x) == b.pool.used(x) for x in gpu.LEVELS)
             assert torch.equal(a.decode(q), b.decode(q))
     assert total > 0
+
+
+def test_calls_go_to_the_current_stream(gpu):
+    """The handle the calls take is the current stream's, the default one and a side one."""
+    torch = _torch()
+    assert gpu._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert gpu._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream

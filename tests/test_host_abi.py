@@ -540,3 +540,12 @@ def test_pool_occupancy_equals_the_accounted_graded_bits(B):
         rates = B.Rates()
         assert B._account(ctypes.byref(c), None, 0, None, ctypes.byref(rates)) == 0
         assert measured == rates.resident_bits
+
+
+def test_stream_handle_without_torchs_raw_lookup(B, monkeypatch):
+    """A torch without the raw-handle lookup: the public call's handle is passed."""
+    class Stream:
+        cuda_stream = 4711
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: Stream)
+    assert B._stream() == 4711
