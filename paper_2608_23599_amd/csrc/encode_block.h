@@ -964,11 +964,15 @@ __device__ __forceinline__ void write_terms(Shared<true> &sh, const Place &pl, d
 
 // Every token's nearest centroid, for fp16 blocks: one MFMA chain per 16-token page gives
 // x . c for the three terms of the four centroids, and |c|^2 - 2 x . c orders the
-// distances.  fp32 accumulation is off by at most 2^-16 |x| |c| (128 products, each
-// addition within 2^-23 of a partial sum below |x| |c|), so a gap between the two
-// nearest of more than 2^-13 |x| |c| + 2^-20 max |c|^2 decides as the fp64 distances do
-// (fp16 subnormals enter these MFMAs as they are); a block with a token inside the margin
-// takes the fp64 distances.  Workgroup-uniform; assign is complete after it.
+// distances.  x . c is off by at most 2^-16 |x| |c| (128 products, each addition within
+// 2^-23 of a partial sum below |x| |c|), twice that in a distance and four times in the gap
+// of two: 2^-14 |x| |c|.  |c|^2 is off by 10 units of 2^-24 |c|^2 (two for the square of a
+// centroid rounded to fp32, two for the pair, six additions over the lanes) and the
+// distance's own rounding adds one: 22 units, below 2^-19 |c|^2, in the gap of two.  A gap
+// between the two nearest of more than 2^-13 |x| |c| + 2^-18 max |c|^2 therefore decides as
+// the fp64 distances do (fp16 subnormals enter these MFMAs as they are); a block with a
+// token inside the margin takes the fp64 distances.  The second term counts for tokens
+// near zero only.  Workgroup-uniform; assign is complete after it.
 __device__ __forceinline__ void assign_fast(Shared<true> &sh, const Place &pl, const h8 (&xa)[4]) {
   const int col = pl.lane & 15;
   f4 S = {0, 0, 0, 0};
@@ -995,7 +999,7 @@ __device__ __forceinline__ void assign_fast(Shared<true> &sh, const Place &pl, c
     if (d2 < bd) { best = 2; sd = bd; bd = d2; } else sd = fminf(sd, d2);
     if (d3 < bd) { best = 3; sd = bd; bd = d3; } else sd = fminf(sd, d3);
     const float xn = sh.l.xn[t];
-    const float margin = fmaf(0x1p-13f * xn, cmr, 0x1p-20f * cm);
+    const float margin = fmaf(0x1p-13f * xn, cmr, 0x1p-18f * cm);
     if (col < 4) sure = sure & (sd - bd > margin);  // false for NaN
     if (col == 0) sh.l.assign[t] = best;
   }

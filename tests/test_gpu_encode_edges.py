@@ -35,6 +35,14 @@ def _block(kind, g):
         x[48] = -x[32]
     elif kind == "near_rows":  # distances that differ in the last places
         x = x[:1] + np.rint(g.standard_normal((P, D))) * 2.0 ** -9
+    elif kind in ("near_zero", "near_zero_ulp"):  # tokens near zero, centroids of (nearly) equal norm
+        far = x[0] * 4
+        x *= 2.0 ** -14
+        for i in (0, 16, 32, 48):
+            x[i] = g.permutation(far) * g.choice((-1.0, 1.0), D)
+        if kind == "near_zero_ulp":
+            x[32, 7] *= 1 + 2.0 ** -10
+            x[1::3] = 0.0
     elif kind == "random":
         x[:, ::31] *= 10
     else:
@@ -42,7 +50,8 @@ def _block(kind, g):
     return x.astype(np.float16).view(np.uint16)
 
 
-KINDS = ("random", "grid", "grid_outliers", "subnormal", "wide", "constant", "equal_rows", "mirrored", "near_rows")
+KINDS = ("random", "grid", "grid_outliers", "subnormal", "wide", "constant", "equal_rows", "mirrored", "near_rows",
+         "near_zero", "near_zero_ulp")
 
 
 def _tensors(seed):
