@@ -641,9 +641,16 @@ __device__ __forceinline__ bool pair_softmax(const AttnParams &p, State &st, f4 
 }
 
 __device__ __forceinline__ uint4 lds16(const uint8_t *a) { return *(const uint4 *)a; }
-__device__ __forceinline__ uint4 gld16(const uint8_t *a) {  // a record's bytes, read once
+// 16 bytes of a lane's chunk in global memory.  NT: nontemporal, for chunks of 16 bytes
+// (int4), whose instruction reads whole lines.  The larger chunks (64 bytes exact, 32 int8)
+// take two or four instructions that read the same lines, which nontemporal loads fetched
+// anew each time: 16384 exact tokens x 8 heads 32.8 -> 21.5 us with plain loads, 16 exact
+// blocks x 64 (sequence, KV head) 32.2 -> 14.8, 64 pages of 64 exact tokens x 64 51.3 ->
+// 32.2, int8 17.8 -> 17.3; int4 is faster with nontemporal ones (16.0 against 16.5).
+template <bool NT = false>
+__device__ __forceinline__ uint4 gld16(const uint8_t *a) {
   typedef uint32_t v4 __attribute__((ext_vector_type(4)));
-  const v4 x = __builtin_nontemporal_load((const v4 *)a);
+  const v4 x = NT ? __builtin_nontemporal_load((const v4 *)a) : *(const v4 *)a;
   return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
@@ -1520,7 +1527,7 @@ __device__ __forceinline__ void tile_words_g(const uint8_t *c, uint32_t *w) {
   } else {
 #pragma unroll
     for (int q = 0; q < BITS; q += 4) {
-      const uint4 a = gld16(c + 4 * q);
+      const uint4 a = gld16<BITS == 4>(c + 4 * q);
       w[q] = a.x; w[q + 1] = a.y; w[q + 2] = a.z; w[q + 3] = a.w;
     }
   }
