@@ -1387,9 +1387,9 @@ __global__ void __launch_bounds__(kThreads, 2) attn_kernel(AttnParams p) {
 // 1300 cycles, a tile pair behind a full ring 600 a unit).  Here a wavefront takes
 // "pieces" of at most two tiles of one block, loads the piece's records straight into
 // registers in MFMA operand order (the packed layout is built for that; scales and zeros
-// pass through LDS) and keeps nothing in flight across pieces: with 16 wavefronts per
-// compute unit the others hide its loads.  No plan kernel, and with all pieces of a (b, KV
-// head) in one workgroup no merge kernel either.
+// pass through LDS) and keeps nothing in flight across pieces: the other wavefronts of its
+// compute unit (8 of a dense read, 12 of pages) hide its loads.  No plan kernel, and with all
+// pieces of a (b, KV head) in one workgroup no merge kernel either.
 struct Piece {
   const uint8_t *kp, *vp;  // records
   int level, t0;           // level (-1: nothing to read), first tile
@@ -1641,8 +1641,9 @@ constexpr size_t short_lds() {
 }
 
 // Workgroup L of the grid serves (b, KV head) L mod units as its workgroup L / units;
-// NT: tiles of a piece (1 for 16-token pages); wavefront w of the W of a (b, KV head) takes a piece and every W-th after it.  `out`: the result
-// itself when one workgroup holds all pieces, else null (partials as attn_kernel's).
+// NT: tiles of a piece (1 for 16-token pages); wavefront w of the W of a (b, KV head) takes
+// a piece and every W-th after it.  `out`: the result itself when one workgroup holds all
+// pieces, else null (partials as attn_kernel's).
 template <int NT, bool PACK, bool VTOK, bool QUEST, bool CERT, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES, QUEST ? 3 : 2) short_kernel(AttnParams p, int64_t npieces, float *out) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -2469,49 +2470,71 @@ struct ShortPlan {
   int waves, nsplit;
   int64_t pieces;  // per (b, KV head)
 };
-// Eight wavefronts a workgroup (four for pages, which are many and small): sixteen need
-// 128 registers, which spills, and a kernel with scratch took 30 us whatever its work.
+// Eight wavefronts a workgroup, four for pages, which are many and small.  The kernel needs
+// more than 128 registers (held to 128 it spills, and with scratch it took 30 us whatever
+// its work), so two wavefronts a SIMD, or three for pages, is all that fits: one dense
+// workgroup a compute unit, three of a page read.
 constexpr int kShortDenseWaves = 8, kShortQuestWaves = 4;
-// Pieces per (b, KV head) that one workgroup takes alone: four per wavefront, about 2 us
-// each, against a merge kernel's 3.2 us and its launch (64 pieces of 2048 tokens: 19.4 us
-// alone, 6.4 + 3.2 us over eight workgroups; the planned kernels 1.5 + 9.7 + 3.2 us).
-constexpr int64_t kShortOne = 32;
-// Pieces over all (b, KV head) of a dense short read: beyond, the planned kernel's ring
-// hides the loads better than another round of pieces (16384 tokens x 8 heads, 4096
-// pieces: 12.5 + 4.0 us against 2.0 + 11.5 + 3.9 us planned).
-constexpr int64_t kShortMax = 4096;
-// Bytes of partials of a Compressed-Quest read, whose reads are short at any context
-// (B = 1: 129 pages at 32k 8.7 -> 6.1 us, 257 at 1M 11.0 -> 7.8 us; B = 8, 8256 pages:
-// 21.2 -> 19.7 us); a larger workspace keeps the planned kernel's wavefronts.
-constexpr int64_t kShortPart = 24ll << 20;
+// Workgroups over all (b, KV head), at most those resident at once on 256 compute units
+// (a constant, so that the workspace's size depends on the shapes alone); beyond, each
+// wavefront takes more pieces.  A workgroup more than that waits for a whole other one and
+// then runs beside idle compute units: with a workgroup per 8 dense pieces, 3072 pieces
+// took 15.4 us (11.9 now), 4096 16.4 (13.2), 4096 exact ones 28.4 (20.6, planned 23.6);
+// with one per 4 pages, 8256 16-token pages 20.0 (16.6), 25728 exact halves of 64-token
+// pages 102.6 (81.2, planned 80.1).
+constexpr int64_t kShortDenseFit = 256, kShortQuestFit = 768;
+static int64_t short_split(int64_t pieces, int waves, int64_t fit, int64_t units) {
+  const int64_t most = fit / units > 1 ? fit / units : 1, n = (pieces + waves - 1) / waves;
+  return n < most ? n : most;
+}
+// Pieces per (b, KV head) that one workgroup takes alone, two per wavefront: a third costs
+// more than a merge kernel's 3.2 us where the records come from HBM (36 heads of 1024
+// exact tokens 20.4 us alone, 13.2 split, 13.0 planned; 640 tokens 14.0, 11.5 and 12.7).
+// At 512 tokens one workgroup is ahead of the planned kernels' 12-13 us from 2 to 64 heads.
+constexpr int64_t kShortOne = 16;
+// Pieces of a dense short read: over all (b, KV head), or per (b, KV head).  Per read of 8 KV
+// heads with caches rotated through HBM, graded / exact ladder, us, short against planned:
+// 1024 pieces 9.5 / 12.5 against 13.8 / 12.8, 2048 10.5 / 14.3 against 14.8 / 14.5, 3072
+// 11.9 / 16.7 against 16.1 / 20.6, 4096 13.2 / 20.6 against 17.3 / 23.6, 8192 17.5 / 26.2
+// against 22.2 / 35.3, 16384 25.7 / 43.6 against 26.3 / 52.3; int2 blocks alone cross over
+// at 8192 to 12288 (22.8 against 21.9), all of them by 24576.  The line lies well below the
+// crossing.  Few pieces of many (b, KV head) are short reads as well: 256 heads of 1024
+// tokens 23.7 against 36.8 us, 1024 heads of them 97.5 against 107.7.
+constexpr int64_t kShortMax = 4096, kShortMaxEach = 32;
+// Heads times workgroups (one per four pages) of a Compressed-Quest read that is short at any
+// context.  Inside, short and planned: 129 pages x 8 heads 9.4 and 11.2 us, 129 x 64 16.6
+// and 21.1 (32-token pages 19.4 and 32.6), 33 x 1024 44.8 and 71.6, exact pages 61.4 and
+// 68.9.  Beyond, exact pages are bound by their bytes, which the planned kernel's ring loads
+// faster (129 x 1024: 226.8 and 203.4).
+constexpr int64_t kShortQuestMax = 47304;
 static ShortPlan short_plan(const gkv_cache *c, int32_t topk, int64_t T, int32_t nres) {
   const int64_t units = (int64_t)c->B * c->Hkv;
   ShortPlan s = {0, 0, 0};
   if (topk > 0) {
     if (nres > 0) return s;  // the residual rows of a page: the planned kernel's lists
     s.pieces = ((int64_t)topk + 1) * (c->page == 64 ? 2 : 1);
-    const int64_t nsplit = (s.pieces + kShortQuestWaves - 1) / kShortQuestWaves;
-    if (nsplit > kMaxSplits) return s;  // more than the merge holds
-    if (units * nsplit * (c->Hq / c->Hkv) * kPart * 4 > kShortPart) return s;
+    const int64_t groups = (s.pieces + kShortQuestWaves - 1) / kShortQuestWaves;
+    if (groups > kMaxSplits || units * groups * (c->Hq / c->Hkv) > kShortQuestMax) return s;
     s.waves = kShortQuestWaves;
-    s.nsplit = (int)nsplit;
+    s.nsplit = (int)short_split(s.pieces, s.waves, kShortQuestFit, units);
     return s;
   }
   s.pieces = 2 * ((T + P - 1) / P + (nres + P - 1) / P);
-  if (s.pieces > kShortOne && units * s.pieces > kShortMax) return s;
-  const int64_t nsplit = s.pieces <= kShortOne ? 1 : (s.pieces + kShortDenseWaves - 1) / kShortDenseWaves;
-  if (nsplit > kMaxSplits) return s;  // one long sequence of one KV head: more than the merge holds
+  if (s.pieces > kShortMaxEach && units * s.pieces > kShortMax) return s;
+  const int64_t groups = (s.pieces + kShortDenseWaves - 1) / kShortDenseWaves;
+  if (groups > kMaxSplits) return s;  // one long sequence of one KV head: more than the merge holds
   s.waves = kShortDenseWaves;
-  s.nsplit = (int)nsplit;
+  s.nsplit = s.pieces <= kShortOne ? 1 : (int)short_split(s.pieces, s.waves, kShortDenseFit, units);
   return s;
 }
 // Workgroups per (b, KV head) of any short read of the cache (the layout's capacity).
 static int short_ncap(const gkv_cache *c, int32_t topk) {
   if (topk > 0) return short_plan(c, topk, 0, 0).nsplit;
-  const int64_t most = kShortMax / ((int64_t)c->B * c->Hkv);
+  const int64_t units = (int64_t)c->B * c->Hkv;
+  int64_t most = kShortMax / units;
+  if (most < kShortMaxEach) most = kShortMaxEach;
   const int64_t pieces = 2 * ((int64_t)c->nblk_cap + (c->nres_cap + P - 1) / P);
-  const int64_t n = (pieces < most ? pieces : most) / kShortDenseWaves + 1;
-  return (int)(n < kMaxSplits ? n : kMaxSplits);
+  return (int)short_split(pieces < most ? pieces : most, kShortDenseWaves, kShortDenseFit, units);
 }
 
 // Workspace layout, sized by the cache capacity so that it does not move as T grows:

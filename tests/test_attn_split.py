@@ -57,6 +57,9 @@ def test_splits_fit_the_merge_and_the_workspace(B, shapes):
             assert e == -6 and s.get("topk"), (s, e)  # more read tiles than the call accepts
             continue
         seen.add(e["waves"] == PLANNED)
+        if e["waves"] != PLANNED and e["nsplit"] > 1:  # resident at once: one dense workgroup on each
+            # of 256 compute units, three of a page read
+            assert s["batch"] * s["kv"] * e["nsplit"] <= (768 if s.get("topk") else 256), (s, e)
         assert 1 <= e["nsplit"] <= e["limit"] == 256, (s, e)
         assert e["part"] >= 256 and e["part_end"] <= e["total"], (s, e)
         assert e["lists_end"] <= e["total"] and (e["waves"] != PLANNED or e["part_end"] <= e["lists"]), (s, e)

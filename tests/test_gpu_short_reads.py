@@ -1,6 +1,7 @@
 """Dense reads at the sizes where the read changes kernels: one workgroup per (sequence,
-KV head) up to 32 two-tile pieces (16 blocks), several workgroups up to 4096 pieces over all
-of them, the planned kernel beyond; ragged lengths, residual rows, values per token and
+KV head) up to 16 two-tile pieces (8 blocks), several workgroups up to 4096 pieces over all
+of them, with more than one piece a wavefront where more workgroups than are resident would
+be needed, the planned kernel beyond; ragged lengths, residual rows, values per token and
 groups of more than 8 heads in each.  Against the oracle within the attention tolerance, and
 the staged calls and the certificate read against the plain call bit for bit."""
 import numpy as np
@@ -22,11 +23,13 @@ def _staged(gpu, cache, q):
     return out
 
 
-# blocks: 16 is the last one-workgroup read, 17 the first split one; with 8 KV heads 256
-# blocks make 4096 pieces and 257 go to the planned kernel
+# blocks: 8 is the last one-workgroup read, 9 the first split one; with 8 KV heads 128 blocks
+# are one piece a wavefront of 32 workgroups each, 129 some second ones, 256 make 4096 pieces
+# and 257 go to the planned kernel
 @pytest.mark.parametrize("prof", ["tiny", "graded"])
 @pytest.mark.parametrize("T,Hq,Hkv", [(1, 4, 2), (17, 4, 2), (64, 32, 2), (64 * 15 + 33, 12, 2), (64 * 16, 12, 2),
-                                      (64 * 16 + 1, 12, 2), (64 * 40 - 7, 20, 2), (64 * 256, 8, 8),
+                                      (64 * 16 + 1, 12, 2), (64 * 40 - 7, 20, 2), (64 * 8, 20, 2),
+                                      (64 * 8 + 1, 20, 2), (64 * 128 + 1, 8, 8), (64 * 256, 8, 8),
                                       (64 * 256 + 1, 8, 8)])
 def test_dense_reads_across_the_kernels(gpu, T, Hq, Hkv, prof):
     import torch
@@ -127,3 +130,24 @@ def test_many_pages_at_the_merge_limit(gpu, page, topk, Hq, Hkv):
         uc = ocache.UnitCache(ks[0, h], vs[0, h], lv)
         ref = uc.decode_quest(q_group(q, 0, h, G), pages[0, h].cpu().numpy(), page)
         assert max_err(out[0, h * G:(h + 1) * G], ref) <= TOL
+
+
+# 64 (sequence, KV head) share 768 workgroups: 12 each, whose 48 wavefronts take a piece each
+# up to 48 pieces and more beyond; 800 leave one workgroup each
+@pytest.mark.parametrize("B,Hkv,page,topk", [(16, 4, 16, 47), (16, 4, 16, 48), (16, 4, 32, 100), (16, 4, 64, 60),
+                                             (100, 8, 16, 21)])
+def test_pages_beyond_one_piece_a_wavefront(gpu, B, Hkv, page, topk):
+    T = page * (topk + 9) + 3
+    G = 4
+    ks, vs = kv_all(76, 1, Hkv, T)
+    ks, vs = np.repeat(ks, B, 0), np.repeat(vs, B, 0)
+    lv = olad.ladder("tiny", T)
+    cache = gpu.GradedCache.build(ks, vs, Hq=Hkv * G, levels=lv, page=page)
+    q = synth.queries(76, B, Hkv * G)
+    pages = cache.quest_select(q, topk)
+    out = cache.decode(q, pages=pages)
+    assert np.array_equal(out.cpu().numpy(), cache.decode(q, pages=pages).cpu().numpy())
+    for b, h in ((0, 0), (B - 1, Hkv - 1)):
+        uc = ocache.UnitCache(ks[b, h], vs[b, h], lv)
+        ref = uc.decode_quest(q_group(q, b, h, G), pages[b, h].cpu().numpy(), page)
+        assert max_err(out[b, h * G:(h + 1) * G].cpu().numpy(), ref) <= TOL
