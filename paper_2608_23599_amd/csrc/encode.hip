@@ -334,6 +334,9 @@ __global__ void __launch_bounds__(kThreads) boxes_kernel(const uint16_t *__restr
 // quarters turned in LDS and an int8 record staged whole (11 wavefronts a compute unit),
 // 338.3 us as it is (12 wavefronts); with one quarter in flight (15 wavefronts) 353.3 us,
 // with the registers held to 128 (15 wavefronts, row loads spilled) 425.8 us.
+// A chunk staged in parts shares its lines among them: with plain loads, the next part's
+// under way while one is used, the selection of 65536 exact tokens x 16 heads takes 140 us
+// (nontemporal, loaded where needed: 209), int8 ones 107 (113).
 constexpr int kRdGroup = 16 * 4 + 4;
 
 struct RdShared {
@@ -348,12 +351,14 @@ __device__ __forceinline__ double h2d(uint32_t bits16) {
 
 // Stage the 256 chunks of a record, WPC words of each (chunk ck's at word
 // ck * src_wpc + src_off of `src`), into the group layout: WPC 16-byte pieces a lane.
-template <int WPC>
+// NT: whole chunks, whose lines are read once.
+template <bool NT, int WPC>
 __device__ __forceinline__ void rd_load(bw4 (&x)[WPC], const uint8_t *src, int src_wpc, int src_off, int lane) {
 #pragma unroll
   for (int i = 0; i < WPC; ++i) {
     const int w0 = (i * 64 + lane) * 4;  // staged word index without padding
-    x[i] = __builtin_nontemporal_load((const bw4 *)(src + ((int64_t)(w0 / WPC) * src_wpc + src_off + w0 % WPC) * 4));
+    const bw4 *at = (const bw4 *)(src + ((int64_t)(w0 / WPC) * src_wpc + src_off + w0 % WPC) * 4);
+    x[i] = NT ? __builtin_nontemporal_load(at) : *at;
   }
 }
 template <int WPC>
@@ -429,15 +434,16 @@ __device__ __forceinline__ void rd_chain(double &e, uint32_t *tr, RdRows &rows, 
   for (int q = 0; q < 4; ++q) rd_quarter(e, tr, rows, q, lane, vhat);
 }
 
-// The chain over a record staged in 4 / Q parts of Q row quarters.
+// The chain over a record staged in 4 / Q parts of Q row quarters, the next part in flight.
 template <int Q, class F>
 __device__ __forceinline__ void rd_chain_parts(double &e, RdShared &S, RdRows &rows, const uint8_t *src,
                                                int src_wpc, int lane, F vhat) {
+  bw4 x[4];
+  rd_load<false>(x, src, src_wpc, 0, lane);
 #pragma unroll
   for (int q0 = 0; q0 < 4; q0 += Q) {
-    bw4 x[4];
-    rd_load(x, src, src_wpc, 4 * (q0 / Q), lane);
     rd_store(S.w, x, lane);
+    if (q0 + Q < 4) rd_load<false>(x, src, src_wpc, 4 * (q0 / Q + 1), lane);
     __syncthreads();
 #pragma unroll
     for (int q = q0; q < q0 + Q; ++q) rd_quarter(e, S.tr, rows, q, lane, vhat);
@@ -518,13 +524,13 @@ __global__ void __launch_bounds__(64) rd_score_kernel(const uint16_t *__restrict
       GKV_RD_INT(8, rd_chain_parts<2>, S, rows, codes, 8, lane);
     } else if (lv == GKV_INT4) {
       bw4 x[4];
-      rd_load(x, codes, 4, 0, lane);
+      rd_load<true>(x, codes, 4, 0, lane);
       rd_store(S.w, x, lane);
       __syncthreads();
       GKV_RD_INT(4, rd_chain, S.tr, rows, lane);
     } else {
       bw4 x[2];
-      rd_load(x, codes, 2, 0, lane);
+      rd_load<true>(x, codes, 2, 0, lane);
       rd_store(S.w, x, lane);
       __syncthreads();
       GKV_RD_INT(2, rd_chain, S.tr, rows, lane);
