@@ -16,6 +16,11 @@ def _mass(kind, shape, seed):
     m = np.exp(3.0 * g.standard_normal(shape)).astype(np.float32)
     if kind == "zeros":  # most scores are 0 and tie
         m[g.random(shape) < 0.99] = 0.0
+    elif kind == "signed":  # above, at and below the zeros that tie at the last place
+        r = g.random(shape)
+        m[r < 0.7] = 0.0
+        m[r < 0.2] = -1.0
+        m[r > 0.71] = 0.0
     elif kind == "same":  # every score is 0: one bucket holds all
         m[:] = 0.0
     elif kind == "wide":  # scores from below the lowest bucket's to the largest masses
@@ -32,7 +37,7 @@ def _mass(kind, shape, seed):
 # (16448, 8192) ends in registers or streamed by its list's length, 12000 always streamed
 @pytest.mark.parametrize("T,n", [(8192, 5000), (8193, 4096), (8193, 4097), (16448, 8192), (20011, 12000),
                                  (20011, 20011), (40000, 1700), (131071, 2621)])
-@pytest.mark.parametrize("kind", ["spread", "zeros", "same", "wide", "odd"])
+@pytest.mark.parametrize("kind", ["spread", "zeros", "signed", "same", "wide", "odd"])
 def test_selection_follows_the_keys(gpu, T, n, kind):
     import torch
     B, H = (2, 2) if T < 131071 else (1, 1)
