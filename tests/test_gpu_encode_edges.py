@@ -124,3 +124,112 @@ def test_demotion_in_place(gpu, chain, per_token):
             for t in (0, 1):
                 assert inplace.record_bytes(0, 0, i, t) == apart.record_bytes(0, 0, i, t), (lv, KINDS[i % len(KINDS)], t)
     assert np.array_equal(inplace.cert.cpu().numpy(), apart.cert.cpu().numpy())
+
+
+# ---------------------------------------------------------------- infinities and NaN
+# The encoder's rules where the oracle's numpy ones differ: a NaN is ignored by a group's
+# minimum and maximum unless it is the group's first element, then both are NaN; a quotient
+# that is NaN gives code 0; a centroid is nearer only where its distance compares below.
+
+
+def _odd_block(kind, g):
+    b = g.standard_normal((P, D)).astype(np.float16).view(np.uint16)
+    def put(n, bits, rows):
+        b[g.choice(rows, n), g.integers(0, D, n)] = g.choice(np.array(bits, np.uint16), n)
+    inf, nan = (0x7C00, 0xFC00), (0x7E00, 0xFE00, 0x7E55)
+    every = np.arange(P)
+    if kind == "inf":
+        put(1, inf, every)
+    elif kind == "infs":
+        put(40, inf, every)
+    elif kind == "nan":
+        put(1, nan, every[1:])
+    elif kind == "nans":
+        put(40, nan, every)
+    elif kind == "first":  # a channel's first row, a token's first channel
+        put(5, nan + inf, every[:1])
+        b[20:24, 0] = (0x7E00, 0x7C00, 0xFC00, 0xFE00)
+    elif kind == "seeds":  # the rows that the centroids start from
+        put(9, nan + inf, every[::16])
+    elif kind == "lines":
+        b[:, 5], b[:, 9], b[:, 11], b[3], b[17] = 0x7E00, 0x7C00, 0xFC00, 0xFE00, 0x7C00
+    elif kind == "largest":
+        b[:] = g.choice(np.array((0x7BFF, 0xFBFF), np.uint16), (P, D))
+    else:
+        b[:] = {"all_nan": 0x7E00, "all_inf": 0x7C00}[kind]
+    return b
+
+
+ODD = ("inf", "infs", "nan", "nans", "first", "seeds", "lines", "largest", "all_nan", "all_inf")
+
+
+def _f16(x):
+    return (x + 0.0).astype(np.float16)  # -0 gives +0
+
+
+def _ref_scalar(x, bits, axis):
+    x = x if axis == 0 else x.T
+    first = np.isnan(x[0])
+    with np.errstate(all="ignore"):
+        mn, mx = np.fmin.reduce(x, 0), np.fmax.reduce(x, 0)
+        mn[first] = mx[first] = np.nan
+        q = (1 << bits) - 1
+        z, s = _f16(mn), _f16((mx - mn) / q)
+        t = np.rint((x - z.astype(np.float64)) / s.astype(np.float64))
+        t = np.where(np.isnan(t) | (s == 0), 0, np.clip(t, 0, q)).astype(np.int32)
+    return (t if axis == 0 else t.T), s, z
+
+
+def _ref_lloyd(x, k):
+    def nearest(c):
+        d = np.zeros((P, k))
+        for ch in range(D):
+            d = d + (x[:, ch, None] - c[None, :, ch]) ** 2
+        best = np.zeros(P, np.int32)
+        for j in range(1, k):
+            best = np.where(d[:, j] < d[np.arange(P), best], j, best)
+        return best
+
+    with np.errstate(all="ignore"):
+        if k == 1:
+            return _f16(np.add.accumulate(x, 0)[-1:] / P), np.zeros(P, np.int32)
+        c, prev = x[::P // k].copy(), None
+        for _ in range(10):
+            a = nearest(c)
+            if prev is not None and np.array_equal(a, prev):
+                break
+            prev = a
+            for j in range(k):
+                if (a == j).any():
+                    c[j] = np.add.accumulate(x[a == j], 0)[-1] / (a == j).sum()
+        c = _f16(c)
+        return c, nearest(c.astype(np.float64))
+
+
+@pytest.mark.parametrize("per_token", (False, True))
+@pytest.mark.parametrize("level,demoted", [(lv, d) for lv in (16, 8, 4, 2, 1, 0) for d in (False, True) if lv < 16 or not d])
+def test_infinities_and_nan(gpu, level, demoted, per_token):
+    """Encoded from rows, and demoted from an exact record."""
+    g = np.random.default_rng(300 + level)
+    k, v = (np.concatenate([_odd_block(kind, g) for kind in ODD])[None, None] for _ in range(2))
+    n = len(ODD)
+    cache = gpu.GradedCache.build(k, v, Hq=1, levels=np.full(n, 16 if demoted else level, np.int8),
+                                  v_per_token=per_token, slack={level: n})
+    if demoted:
+        cache.demote([(0, 0, i) for i in range(n)], [level] * n)
+    for i in range(n):
+        for t in (0, 1):
+            x = (k, v)[t][0, 0, i * P:(i + 1) * P].view(np.float16).astype(np.float64)
+            got = cache.record(0, 0, i, t)
+            what = f"{ODD[i]} {t}"
+            if level == 16:
+                np.testing.assert_array_equal(got["values"], x, err_msg=what)
+            elif level in (1, 0):
+                cent, ids = _ref_lloyd(x, 4 if level else 1)
+                np.testing.assert_array_equal(got["cent16"].view(np.float16), cent, err_msg=what)
+                np.testing.assert_array_equal(got["ids"], ids, err_msg=what)
+            else:
+                codes, s, z = _ref_scalar(x, level, 1 if per_token and t else 0)
+                np.testing.assert_array_equal(got["s16"].view(np.float16), s, err_msg=what)
+                np.testing.assert_array_equal(got["z16"].view(np.float16), z, err_msg=what)
+                np.testing.assert_array_equal(got["codes"], codes, err_msg=what)
