@@ -9,6 +9,7 @@ from oracle import fp16 as ofp16, ladder as olad, quest as oquest, residual as o
 from oracle import accounting as oacc
 from paper_2608_23599_amd import synth
 from tests._util import TOL, kv_all, oracle_units, compare_record, q_group, max_err
+from tests.test_attn_split import PLANNED, extents
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +21,11 @@ def _torch():
 
 def _build(gpu, ks, vs, Hq, levels, **kw):
     return gpu.GradedCache.build(ks, vs, Hq=Hq, levels=levels, device="cuda", **kw)
+
+
+def _planned(gpu, c):
+    """Whether a dense read of the cache runs the planned kernel (else the short one)."""
+    return extents(gpu, c.B, c.Hkv, c.Hq // c.Hkv, c.T, c.nblk_cap, int(c.c.nres), c.nres_cap, c.page)["waves"] == PLANNED
 
 
 def _order_keys(s):
@@ -277,7 +283,8 @@ def test_demote_chain_bit_exact(gpu):
         assert max_err(out[b, 2 * h:2 * h + 2], uc.decode_dense(q_group(q, b, h, 2))) <= TOL
 
 
-def test_dense_plan_kept_through_appends_inside_a_block(gpu):
+@pytest.mark.parametrize("Bn", [1, 26])  # a short read (which keeps a tag but no plan), a planned one
+def test_dense_plan_kept_through_appends_inside_a_block(gpu, Bn):
     """An append that opens no block (and demotes nothing) leaves the block tables and
     the version as they were, so a dense read keeps the plan in its workspace: the plan
     covers the last block whole and the attention masks its tokens past the length.
@@ -286,10 +293,11 @@ def test_dense_plan_kept_through_appends_inside_a_block(gpu):
     Hq, Hkv = 8, 2
     T0 = 64 * 40 - 3
     steps = 12  # step 3 opens block 40
-    ks, vs = kv_all(6, 1, Hkv, T0 + steps)
+    ks, vs = (np.repeat(x, Bn, 0) for x in kv_all(6, 1, Hkv, T0 + steps))
     lv = olad.ladder("graded", T0)
     cache = _build(gpu, ks[:, :, :T0], vs[:, :, :T0], Hq, lv, extra_blocks=2,
-                   slack={16: 8, 8: 8, 4: 8, 2: 8, 1: 8})
+                   slack={x: 8 * Bn for x in (16, 8, 4, 2, 1)})
+    assert _planned(gpu, cache) == (Bn > 1)
     ucs = {h: ocache.UnitCache(ks[0, h, :T0], vs[0, h, :T0], lv) for h in range(Hkv)}
     G = Hq // Hkv
     kept = 0
@@ -304,7 +312,7 @@ def test_dense_plan_kept_through_appends_inside_a_block(gpu):
         else:
             assert int(cache.c.version) != v0
         kept += int(cache.c.version) == v0
-        q = synth.queries(6, 1, Hq, step=s)
+        q = synth.queries(6, Bn, Hq, step=s)
         out = cache.decode(q)
         ws = cache._ws[(1, 0)]
         cache._ws[(1, 0)] = _torch().zeros_like(ws)
@@ -312,9 +320,10 @@ def test_dense_plan_kept_through_appends_inside_a_block(gpu):
         cache._ws[(1, 0)] = ws
         assert _torch().equal(out, fresh)
         out = out.cpu().numpy()
-        for h in range(Hkv):
-            ref = ucs[h].decode_dense(q_group(q, 0, h, G))
-            assert max_err(out[0, h * G:(h + 1) * G], ref) <= TOL
+        for b in {0, Bn - 1}:
+            for h in range(Hkv):
+                ref = ucs[h].decode_dense(q_group(q, b, h, G))
+                assert max_err(out[b, h * G:(h + 1) * G], ref) <= TOL
     assert kept >= steps - 3
 
 
@@ -1071,7 +1080,8 @@ def test_quest128k_b8_full_size_sampled(gpu):
 # ---------------------------------------------------------------- dense plan reuse
 
 
-def test_dense_plan_reuse_follows_the_tables(gpu):
+@pytest.mark.parametrize("Bn,Hq,Hkv,T", [(1, 8, 2, 2048), (8, 32, 8, 2112)])  # a short read, a planned one
+def test_dense_plan_reuse_follows_the_tables(gpu, Bn, Hq, Hkv, T):
     """A dense read reuses the visit plan a workspace holds only for the same table
     state: two caches alternating on one workspace, an append (T grows), a demotion
     (levels and slots change), a residual selection (rows leave their blocks) and a
@@ -1081,18 +1091,20 @@ def test_dense_plan_reuse_follows_the_tables(gpu):
     may lie where a plan was)."""
     import ctypes
     torch = _torch()
-    T, Hq, Hkv = 2048, 8, 2
-    (ka, va), (kb, vb) = kv_all(40, 1, Hkv, T + 1), kv_all(41, 1, Hkv, T)
+    (ka, va), (kb, vb) = kv_all(40, Bn, Hkv, T + 1), kv_all(41, Bn, Hkv, T)
     lv = olad.ladder("tiny", T)
+    slack = {x: 2 * Bn * Hkv for x in (16, 8, 4, 2, 1)}
     A = _build(gpu, ka[:, :, :T], va[:, :, :T], Hq, lv, page=16, extra_blocks=2, nres_cap=64,
-               slack={16: 4, 8: 4, 4: 4, 2: 4, 1: 4})
-    Bc = _build(gpu, kb, vb, Hq, lv, page=16, extra_blocks=2, nres_cap=64, slack={16: 4, 8: 4, 4: 4, 2: 4, 1: 4})
-    q = synth.queries(40, 1, Hq)
+               slack=slack)
+    Bc = _build(gpu, kb, vb, Hq, lv, page=16, extra_blocks=2, nres_cap=64, slack=slack)
+    planned = Bn > 1
+    assert _planned(gpu, A) == _planned(gpu, Bc) == planned
+    q = synth.queries(40, Bn, Hq)
     nbytes = max(A.workspace(1, 0).numel(), A.workspace(1, 32).numel())
     shared = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
 
     def dec(c, pages=None):
-        out = torch.empty((1, Hq, 128), dtype=torch.float32, device="cuda")
+        out = torch.empty((Bn, Hq, 128), dtype=torch.float32, device="cuda")
         topk = 0 if pages is None else int(pages.shape[-1])
         st = gpu._attn(gpu._dptr(gpu._as_bits(q, "cuda")), ctypes.byref(c.c), gpu._dptr(pages), topk,
                        gpu._dptr(out), gpu._dptr(shared), shared.numel(), gpu._stream())
@@ -1105,7 +1117,10 @@ def test_dense_plan_reuse_follows_the_tables(gpu):
 
     def tag():
         torch.cuda.synchronize()
-        return int(shared[:8].cpu().numpy().view(np.uint64)[0])
+        words = shared[:96].cpu().numpy().view(np.uint64)
+        # the last word of a planned read's tag says that the workspace holds a plan
+        assert words[0] == 0 or (words[11] == 0x676b76706c616e31) == planned
+        return int(words[0])
 
     for c in (A, Bc, A, Bc, A):
         assert torch.equal(dec(c), fresh(c))
@@ -1114,7 +1129,7 @@ def test_dense_plan_reuse_follows_the_tables(gpu):
     assert torch.equal(dec(A), fresh(A))
     Bc.demote([(0, 0, 5), (0, 1, 9)], [1, 2])  # int2 -> centroid, int4 -> int2
     assert torch.equal(dec(Bc), fresh(Bc))
-    mass = np.stack([synth.mass_unit(41, 0, h, T) for h in range(Hkv)])[None]
+    mass = np.stack([np.stack([synth.mass_unit(41, b, h, T) for h in range(Hkv)]) for b in range(Bn)])
     Bc.rd_residual_select(kb, vb, mass, 64)
     assert torch.equal(dec(Bc), fresh(Bc))
     assert tag() == Bc.c.version

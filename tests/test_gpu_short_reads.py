@@ -67,7 +67,8 @@ def test_short_reads_with_residual_rows(gpu, T, pct):
         assert max_err(out[0, h * 4:(h + 1) * 4], uc.decode_dense(q_group(q, 0, h, 4))) <= TOL
 
 
-@pytest.mark.parametrize("lens", [(1, 64 * 3, -1, 64 * 9 + 5), (64 * 30, 7, 64 * 16, 64)])
+@pytest.mark.parametrize("lens", [(1, 64 * 3, -1, 64 * 9 + 5), (64 * 30, 7, 64 * 16, 64),
+                                  (64 * 300 + 5, 7, -1, 64 * 130 + 1)])  # the last one: the planned kernel
 def test_short_reads_of_ragged_batches(gpu, lens):
     """Each sequence reads its own pieces; a retired one's output is zero."""
     T, Hq, Hkv = max(lens), 8, 2
@@ -92,14 +93,17 @@ def test_short_reads_of_ragged_batches(gpu, lens):
 
 # 65536 tokens of one unit are 256 workgroups' pieces, the most the merge holds; one token
 # more, or residual pseudo-blocks past 1024 blocks in all, go to the planned kernel
-@pytest.mark.parametrize("T,Hq,nres", [(65536, 4, 0), (65537, 16, 0), (131072, 4, 0), (900 * 64, 4, 124 * 64),
-                                       (900 * 64, 4, 124 * 64 + 1)])
-def test_one_long_unit_at_the_merge_limit(gpu, T, Hq, nres):
+@pytest.mark.parametrize("T,Hq,nres,vtok", [(65536, 4, 0, False), (65537, 16, 0, False), (131072, 4, 0, False),
+                                            (900 * 64, 4, 124 * 64, False), (900 * 64, 4, 124 * 64 + 1, False),
+                                            (65537, 4, 0, True), (65600, 12, 0, True)])
+def test_one_long_unit_at_the_merge_limit(gpu, T, Hq, nres, vtok):
+    """The long ones are the planned kernel's: its certificate for packed and unpacked groups,
+    residual rows and values per token."""
     import torch
     ks, vs = kv_all(74, 1, 1, T)
     lv = olad.ladder("tiny", T)
-    cache = gpu.GradedCache.build(ks, vs, Hq=Hq, levels=lv, nres_cap=nres)
-    uc = ocache.UnitCache(ks[0, 0], vs[0, 0], lv)
+    cache = gpu.GradedCache.build(ks, vs, Hq=Hq, levels=lv, nres_cap=nres, v_per_token=vtok)
+    uc = ocache.UnitCache(ks[0, 0], vs[0, 0], lv, v_per_token=vtok)
     if nres:
         mass = synth.mass_unit(74, 0, 0, T)[None, None].astype(np.float32)
         cache.rd_residual_select(ks, vs, mass, nres)
