@@ -2497,7 +2497,7 @@ constexpr int64_t kShortOne = 16;
 // 1024 pieces 9.5 / 12.5 against 13.8 / 12.8, 2048 10.5 / 14.3 against 14.8 / 14.5, 3072
 // 11.9 / 16.7 against 16.1 / 20.6, 4096 13.2 / 20.6 against 17.3 / 23.6, 8192 17.5 / 26.2
 // against 22.2 / 35.3, 16384 25.7 / 43.6 against 26.3 / 52.3; int2 blocks alone cross over
-// at 8192 to 12288 (22.8 against 21.9), all of them by 24576.  The line lies well below the
+// at 8192 to 12288 (22.8 against 21.9), the other ladders by 24576.  The line lies well below the
 // crossing.  Few pieces of many (b, KV head) are short reads as well: 256 heads of 1024
 // tokens 23.7 against 36.8 us, 1024 heads of them 97.5 against 107.7.
 constexpr int64_t kShortMax = 4096, kShortMaxEach = 32;

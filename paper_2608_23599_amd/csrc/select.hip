@@ -538,7 +538,7 @@ static int64_t sel_ckey_stride(int64_t key_stride) { return key_stride / 2 + kSe
 // to itself, above the negative scores': all its keys are equal, so where the k-th key lies
 // there the list takes no more of them than are kept, and has k entries.
 //
-// 131072 tokens, 2621 kept, 32 units: count, filter and final selection 9.1 + 12.6 + 15.6 us
+// 131072 tokens, 2621 kept, 32 units: count, filter and final selection 9.1 + 13.7 + 13.9 us
 // against 31.5 + 20.6 + 20.5 + 17.0 us for four stages.  The whole selection of these sizes on
 // the graded ladder: masses spread over powers of two 313 us (404 with stages), equal masses,
 // whose scores crowd into few buckets, 320 (415), 1 mass in 700 not zero 358 (666; 1291 with
